@@ -74,7 +74,8 @@ DESCRIPTIONS = {
 SRC_DIR = os.path.join(ROOT, "paper_2012_01170_amd", "csrc")
 PROFILES = os.path.join(ROOT, "profiles")
 # device function -> the name the library's trace hook gives its launch
-TRACE_NAME = {"bwd_ws_kernel": "bwd_fused", "fwd_fused_kernel": "fwd_fused",
+TRACE_NAME = {"bwd_ws_kernel": "bwd_fused",
+              "tile_dw_kernel": "bwd_tile_dw",
               "fwd_reg_kernel": "fwd_fused", "fwd_onehot_kernel": "fwd_fused",
               "dw_reduce_kernel": "bwd_dw_reduce",
               "sample_kernel<true>": "sample", "sample_kernel<false>": "sample_count",
@@ -395,7 +396,8 @@ def featureless_table(n_in, n_out, E, M, P):
     }
 
 
-def kernel_table(kind, plan, n_in, n_out, E, M, ci, co, sf, blocks_bwd=256, npix=0):
+def kernel_table(kind, plan, n_in, n_out, E, M, ci, co, sf, blocks_bwd=256, npix=0,
+                 order="auto"):
     """Kernels of one step: name -> (launches per step, algorithmic bytes, flops, on MFMA).
 
     Bytes count every array the kernel must touch once (gathered rows once per
@@ -441,6 +443,14 @@ def kernel_table(kind, plan, n_in, n_out, E, M, ci, co, sf, blocks_bwd=256, npix
         t["bwd_fused"] = (1, 4 * (n_in + 1) + 4 * E + geo + n_out * co * sf + n_in * ci * sf
                           + W + 4 * n_in * ci, 4 * n_in * M * ci * co, True)
         t["bwd_dw_reduce"] = (1, 4 * M * ci * co, 0, False)
+    elif order != "gemm_first" and 8 <= min(ci, co) and max(ci, co) <= 512:
+        # the tile passes: the input gradient over the inputs, the weight
+        # gradient over the side that the order names
+        t["bwd_tile_df"] = (1, 4 * (n_in + 1) + 4 * E + geo + n_out * co * sf + W
+                            + 4 * n_in * ci, 2 * n_in * M * co * ci, True)
+        rows = n_in if plan["backward_order"] == "spmm_first" else n_out
+        t["bwd_tile_dw"] = (1, 4 * (rows + 1) + 4 * E + geo + n_out * co * sf + n_in * ci * sf
+                            + 4 * M * ci * co, 2 * rows * M * ci * co, True)
     elif plan["backward_order"] == "spmm_first":
         basis_launches += 1
         D = 4 * n_in * M * co
@@ -967,7 +977,8 @@ def main(argv=None):
         tr_bwd = 32                                       # the fused backward's tile rows
         blocks_bwd = max(1, min(256, n_cus, (n_in + tr_bwd - 1) // tr_bwd))
         npix = w["width"] * w["height"] if w["kind"] == "events" else 0
-        table = kernel_table(w["kind"], plan, n_in, n_out, E, M, ci, co, sf, blocks_bwd, npix)
+        table = kernel_table(w["kind"], plan, n_in, n_out, E, M, ci, co, sf, blocks_bwd, npix,
+                             a.order)
         if not in_step:
             for k in ("points_count", "points_fill"):
                 table.pop(k, None)

@@ -555,15 +555,22 @@ const char *sbc_kernel_names(void);
  *   forward_order   SPMM_FIRST: (N F) W;  GEMM_FIRST: N (F W)
  *   backward_order  SPMM_FIRST: D = N^T dY first (dF = D Wt, dW = F^T D);
  *                   GEMM_FIRST: dG = dY W^T first (dF = N^T dG, dW = G^T dY)
- *   *_fused         1 when that pass runs as one fused kernel (gather into
- *                   LDS, basis evaluated inside, MFMA contraction), 0 when it
- *                   runs as separate gather and contraction kernels.
+ *   forward_fused   1 when gather and contraction run in one kernel (basis
+ *                   evaluated inside, nothing of [rows, M*C] in memory), 0
+ *                   when they run as separate kernels.
+ *   backward_fused  1 when both gradients come out of one such kernel, 0 when
+ *                   each has its own: one kernel per gradient with 8 to 512
+ *                   channels (except under an explicit GEMM_FIRST; AUTO's
+ *                   GEMM_FIRST then names the side the weight gradient sums
+ *                   over), else separate gather and contraction kernels.
  * AUTO picks the order with the lower estimated cost: the multiply-adds of
  * the paper's cost table, plus 5e7 multiply-adds (about 5 us, measured) for
  * every kernel launch, a fused pass counting as two launches and a pass of
  * separate gather and contraction kernels as five.  The launch term only
- * matters for small problems, where it prefers the fused pass.  For the
- * backward the estimate is applied to the transposed problem.
+ * matters for small problems, where it prefers the fused pass.  Where a
+ * gather-first pass of one kernel serves any channel count (8 to 512), it is
+ * taken unless there are more result rows than gathered ones.  For the
+ * backward the rule is applied to the transposed problem.
  */
 typedef struct {
     sbc_order forward_order;

@@ -90,6 +90,28 @@ __global__ void __launch_bounds__(256)
 // times w / W_i; the row's [E, 10] values are contiguous.
 constexpr int kWLanes = 16;
 
+// The weight sums alone, W_i of every row (the same sums).
+__global__ void __launch_bounds__(256)
+    weight_sum_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
+                      const int32_t *__restrict__ col_idx, int64_t nnz_bound, sbc_geometry g,
+                      double *__restrict__ wsum) {
+    const int sl = threadIdx.x % kWLanes;
+    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWLanes;
+    if (r >= n_rows) return;  // a group leaves as a whole
+    const int64_t e1 = row_ptr[r + 1] < nnz_bound ? (int64_t)row_ptr[r + 1] : nnz_bound;
+    const int64_t e0 = row_ptr[r] < e1 ? (int64_t)row_ptr[r] : e1;
+    const double inv_r = 1.0 / (double)g.radius;
+    const float qx = g.x_out[3 * r], qy = g.x_out[3 * r + 1], qz = g.x_out[3 * r + 2];
+    double w = 0.0;
+    for (int64_t e = e0 + sl; e < e1; e += kWLanes) {
+        const int64_t j = col_idx[e];
+        w += point_weight(qx, qy, qz, g.x_in[3 * j], g.x_in[3 * j + 1], g.x_in[3 * j + 2], inv_r);
+    }
+#pragma unroll
+    for (int d = kWLanes / 2; d >= 1; d >>= 1) w += __shfl_xor(w, d, kWLanes);
+    if (sl == 0) wsum[r] = w;
+}
+
 __global__ void __launch_bounds__(256)
     weighted_basis_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
                           const int32_t *__restrict__ col_idx, int64_t nnz_bound, sbc_geometry g,
@@ -199,6 +221,18 @@ sbc_status basis_eval_launch(const sbc_csr *csr, const sbc_geometry *g, float *v
                              hipStream_t stream) {
     return basis_launch<false>(csr->n_rows, csr->row_ptr, csr->col_idx, csr->nnz_bound, g, v,
                                stream);
+}
+
+sbc_status weight_sums_launch(const sbc_csr *csr, const sbc_geometry *g, double *wsum,
+                              hipStream_t stream) {
+    if (csr->n_rows <= 0) return SBC_OK;
+    trace_before("basis", stream);
+    hipLaunchKernelGGL(weight_sum_kernel, dim3(grid_for((int64_t)csr->n_rows * kWLanes, 256)),
+                       dim3(256), 0, stream, csr->n_rows, csr->row_ptr, csr->col_idx,
+                       csr->nnz_bound, *g, wsum);
+    SBC_LAUNCH_CHECK();
+    trace_after("basis", stream);
+    return SBC_OK;
 }
 
 sbc_status decay_derivative_launch(const sbc_csr *csr, const sbc_geometry *g, float *v,

@@ -7,9 +7,10 @@
 // Backward, D-route (gather first):  D = [N^(m)T dY]_m [n_in, M*C_out], dF = D Wt, dW = F^T D
 // Backward, G-route (GEMM first):    dG = dY W_flat^T, dF = N^T dG; dW = G^T dY with G = N F
 // Shapes listed in fused.hip run SpMM-first forward and the D-route as fused
-// kernels (basis evaluated inside); other shapes and orders use the generic
-// kernels below, which evaluate the basis into the workspace first when v is
-// NULL.
+// kernels (basis evaluated inside); others of 8 to 512 channels run the
+// gather-first products as tile passes (tile.hpp); what is left, and the
+// contract-first products, use the generic kernels below, which evaluate the
+// basis into the workspace first when v is NULL.
 #include <mutex>
 #include <string>
 
@@ -18,6 +19,7 @@
 #include "fused.hpp"
 #include "gemm.hpp"
 #include "spmm.hpp"
+#include "tile.hpp"
 
 namespace sbc {
 namespace {
@@ -138,11 +140,53 @@ bool route_fused(Route r, int32_t M, int32_t Ci, int32_t Co, bool bf) {
     return false;
 }
 
+// Temporary space of the tile passes (tile.hpp): the weights' fragments, the
+// packed events, the weighted basis's row sums (M = 10) and, for the backward,
+// the weight gradient's partial sums.
+struct TileWs {
+    void *frag, *packed, *part;
+    double *wsum;
+};
+
+TileWs carve_tile(void *base, Route r, int32_t n_out, int32_t n_in, int32_t M, int32_t Ci,
+                  int32_t Co, bool bf, size_t *bytes) {
+    Carver cv(base);
+    TileWs w{};
+    const int32_t n = n_out > n_in ? n_out : n_in;
+    w.frag = cv.take<char>(r == kFwdSpmm ? tile_frag_bytes(M, Ci, Co, bf)
+                                         : tile_frag_bytes(M, Co, Ci, bf));
+    w.packed = cv.take<int4>((size_t)(M % 8 == 0 && n > 0 ? n : 0));
+    w.wsum = cv.take<double>((size_t)(M == 10 ? n_out : 0));
+    if (r == kBwdD) w.part = cv.take<char>(tile_dw_bytes(n_in, M, Ci, Co));
+    if (r == kBwdG) w.part = cv.take<char>(tile_dw_bytes(n_out, M, Co, Ci));
+    if (bytes) *bytes = cv.used;
+    return w;
+}
+
+// Shapes that take the tile passes where the route allows it: those without a
+// fused kernel of their own.
+bool tile_shape(Route r, int32_t M, int32_t Ci, int32_t Co, bool bf) {
+    return tile_available(M, Ci, Co) && !route_fused(r, M, Ci, Co, bf);
+}
+
+// Whether a route runs as tile passes: the gather-first ones, and under AUTO
+// the G-route, whose input gradient then gathers first all the same (its
+// weight gradient still sums over the n_out rows).
+bool route_tile(Route r, int32_t M, int32_t Ci, int32_t Co, bool bf, sbc_order order) {
+    if (r == kFwdGemm || (r == kBwdG && order != SBC_ORDER_AUTO)) return false;
+    return tile_shape(r, M, Ci, Co, bf);
+}
+
 size_t route_bytes(Route r, int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t Ci,
-                   int32_t Co, bool bf) {
+                   int32_t Co, bool bf, sbc_order order) {
+    if (route_tile(r, M, Ci, Co, bf, order)) {
+        size_t b = 0;
+        carve_tile(nullptr, r, n_out, n_in, M, Ci, Co, bf, &b);
+        return b;
+    }
     if (route_fused(r, M, Ci, Co, bf))
         return r == kFwdSpmm
-                   ? fused_forward_workspace_bytes(M, Ci, Co, n_out > n_in ? n_out : n_in, nnz)
+                   ? fused_forward_workspace_bytes(n_out > n_in ? n_out : n_in)
                    : fused_workspace_bytes(M, Ci, Co, n_out > n_in ? n_out : n_in, nnz);
     size_t b = 0;
     carve_route(nullptr, r, n_out, n_in, nnz, M, Ci, Co, &b);
@@ -156,6 +200,12 @@ size_t route_bytes(Route r, int32_t n_out, int32_t n_in, int64_t nnz, int32_t M,
 // pass of separate gather and contraction kernels as kSplitLaunches.  The
 // launch term only decides between orders whose multiply-adds differ by less
 // than a few launches' worth, i.e. small problems, where the fused pass wins.
+// Shapes of the tile passes gather first unless there are more result rows
+// than gathered ones: the tile pass keeps the intermediate on the CU, where
+// the separate kernels write and read M C floats a row, which costs more than
+// the multiply-adds a contraction first would save (in place, M 8, 128 -> 32
+// channels, 16 edges a row).  With more result rows (up-sampling) the
+// multiply-adds decide as for the others.
 constexpr double kLaunchMacs = 5e7;
 constexpr double kFusedLaunches = 2, kSplitLaunches = 5;
 
@@ -170,6 +220,7 @@ Route forward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t
                     sbc_order order, bool bf) {
     if (order == SBC_ORDER_SPMM_FIRST) return kFwdSpmm;
     if (order == SBC_ORDER_GEMM_FIRST) return kFwdGemm;
+    if (n_out <= n_in && tile_shape(kFwdSpmm, M, Ci, Co, bf)) return kFwdSpmm;
     const double spmm = order_macs(n_out, n_in, nnz, M, Ci, Co, true) +
                         kLaunchMacs * (route_fused(kFwdSpmm, M, Ci, Co, bf) ? kFusedLaunches
                                                                              : kSplitLaunches);
@@ -185,6 +236,7 @@ Route backward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_
                      sbc_order order, bool bf) {
     if (order == SBC_ORDER_SPMM_FIRST) return kBwdD;
     if (order == SBC_ORDER_GEMM_FIRST) return kBwdG;
+    if (n_in <= n_out && tile_shape(kBwdD, M, Ci, Co, bf)) return kBwdD;
     const double d = order_macs(n_in, n_out, nnz, M, Co, Ci, true) +
                      kLaunchMacs * (route_fused(kBwdD, M, Ci, Co, bf) ? kFusedLaunches
                                                                        : kSplitLaunches);
@@ -249,7 +301,10 @@ extern "C" sbc_status sbc_conv_plan(int32_t n_out, int32_t n_in, int64_t nnz_bou
     const Route b = backward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
     plan->forward_order = f == kFwdSpmm ? SBC_ORDER_SPMM_FIRST : SBC_ORDER_GEMM_FIRST;
     plan->backward_order = b == kBwdD ? SBC_ORDER_SPMM_FIRST : SBC_ORDER_GEMM_FIRST;
-    plan->forward_fused = route_fused(f, M, C_in, C_out, bf) ? 1 : 0;
+    plan->forward_fused = route_fused(f, M, C_in, C_out, bf) ||
+                                  route_tile(f, M, C_in, C_out, bf, order)
+                              ? 1
+                              : 0;
     plan->backward_fused = route_fused(b, M, C_in, C_out, bf) ? 1 : 0;
     return SBC_OK;
 }
@@ -261,13 +316,26 @@ extern "C" size_t sbc_conv_workspace_size(int32_t n_out, int32_t n_in, int64_t n
     const bool bf = dtype == SBC_BF16;
     const Route f = forward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
     const Route b = backward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
-    const size_t a = route_bytes(f, n_out, n_in, nnz_bound, M, C_in, C_out, bf);
-    const size_t c = route_bytes(b, n_out, n_in, nnz_bound, M, C_in, C_out, bf);
+    const size_t a = route_bytes(f, n_out, n_in, nnz_bound, M, C_in, C_out, bf, order);
+    const size_t c = route_bytes(b, n_out, n_in, nnz_bound, M, C_in, C_out, bf, order);
     return a > c ? a : c;
 }
 
 namespace sbc {
 namespace {
+
+// Basis mode of the tile passes and their geometry (for the weighted basis
+// with its row sums, which depend on whole rows).
+sbc_status tile_geometry(const sbc_csr *csr, const float *v, const sbc_geometry *geometry,
+                         const TileWs &ws, hipStream_t stream, KGeo *g, int *mode) {
+    *mode = v ? 0 : (int)geometry->basis + 1;
+    SBC_TRY(make_kgeo(csr, v, geometry, ws.packed, stream, g));
+    if (!v && geometry->basis == SBC_BASIS_WMONO10) {
+        SBC_TRY(weight_sums_launch(csr, geometry, ws.wsum, stream));
+        g->wsum = ws.wsum;
+    }
+    return SBC_OK;
+}
 
 // The forward pass with its temporary space in `workspace` (workspace_bytes of it).
 sbc_status conv_forward(const sbc_csr *csr, const float *v, const sbc_geometry *geometry,
@@ -281,9 +349,18 @@ sbc_status conv_forward(const sbc_csr *csr, const float *v, const sbc_geometry *
     const int32_t n_out = csr->n_rows, n_in = csr->n_cols;
     const bool bf = dtype == SBC_BF16;
     const Route r = forward_route(n_out, n_in, csr->nnz_bound, M, C_in, C_out, order, bf);
-    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf);
+    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf, order);
     if (!workspace || workspace_bytes < need)
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_conv_workspace_size()");
+    if (route_tile(r, M, C_in, C_out, bf, order)) {
+        const TileWs ws = carve_tile(workspace, r, n_out, n_in, M, C_in, C_out, bf, nullptr);
+        KGeo g;
+        int mode;
+        SBC_TRY(tile_geometry(csr, v, geometry, ws, stream, &g, &mode));
+        return tile_contract(TilePattern{n_out, csr->row_ptr, csr->col_idx, nullptr, false}, v, g,
+                             mode, M, F, W, false, bf, C_in, C_out, Y, ws.frag, stream,
+                             "fwd_fused");
+    }
     if (route_fused(r, M, C_in, C_out, bf))
         return fused_forward(csr, v, geometry, M, F, W, bf, C_in, C_out, Y, workspace, stream);
 
@@ -366,7 +443,8 @@ extern "C" sbc_status sbc_conv_forward_noalloc(const sbc_csr *csr, const float *
     const bool bf = dtype == SBC_BF16;
     const Route r = forward_route(csr->n_rows, csr->n_cols, csr->nnz_bound, M, C_in, C_out, order,
                                   bf);
-    const size_t need = route_bytes(r, csr->n_rows, csr->n_cols, csr->nnz_bound, M, C_in, C_out, bf);
+    const size_t need = route_bytes(r, csr->n_rows, csr->n_cols, csr->nnz_bound, M, C_in, C_out, bf,
+                                    order);
     if (need > kScratchBytes)
         return fail(SBC_ERR_WORKSPACE, "this forward needs " + std::to_string(need) +
                                            " bytes of temporary space; the library's static "
@@ -404,9 +482,26 @@ extern "C" sbc_status sbc_conv_backward(const sbc_csr *csr, const sbc_csc *csc, 
     const int32_t n_out = csr->n_rows, n_in = csr->n_cols;
     const bool bf = dtype == SBC_BF16;
     const Route r = backward_route(n_out, n_in, csr->nnz_bound, M, C_in, C_out, order, bf);
-    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf);
+    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf, order);
     if (!workspace || workspace_bytes < need)
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_conv_workspace_size()");
+    if (route_tile(r, M, C_in, C_out, bf, order)) {
+        const TileWs ws = carve_tile(workspace, r, n_out, n_in, M, C_in, C_out, bf, nullptr);
+        KGeo g;
+        int mode;
+        SBC_TRY(tile_geometry(csr, v, geometry, ws, stream, &g, &mode));
+        const TilePattern rows{n_out, csr->row_ptr, csr->col_idx, nullptr, false};
+        const TilePattern cols{n_in, csc->col_ptr, csc->row_idx, csc->edge_perm, true};
+        if (dF)
+            SBC_TRY(tile_contract(cols, v, g, mode, M, dY, W, true, bf, C_out, C_in, dF, ws.frag,
+                                  stream, "bwd_tile_df"));
+        if (dW)
+            SBC_TRY(r == kBwdD ? tile_weight_gradient(cols, v, g, mode, M, F, dY, bf, C_in, C_out,
+                                                      dW, ws.part, stream, "bwd_tile_dw")
+                               : tile_weight_gradient(rows, v, g, mode, M, dY, F, bf, C_in, C_out,
+                                                      dW, ws.part, stream, "bwd_tile_dw"));
+        return SBC_OK;
+    }
     if (route_fused(r, M, C_in, C_out, bf))
         return fused_backward(csr, csc, v, geometry, M, F, W, dY, bf, C_in, C_out, dF, dW,
                               workspace, stream);
@@ -494,6 +589,29 @@ struct DecayWs {
     float *v, *G, *dWp, *partial;
 };
 
+// The decay gradient through the tile passes: dW' over the transposed pattern
+// where it is given, else over the rows.
+struct DecayTileWs {
+    void *packed, *part;
+    float *dWp;
+};
+
+DecayTileWs carve_decay_tile(void *base, int32_t n, int32_t M, int32_t Ci, int32_t Co,
+                             size_t *bytes) {
+    Carver cv(base);
+    DecayTileWs w;
+    w.packed = cv.take<int4>((size_t)n);
+    w.dWp = cv.take<float>((size_t)M * Ci * Co);
+    const size_t a = tile_dw_bytes(n, M, Ci, Co), b = tile_dw_bytes(n, M, Co, Ci);
+    w.part = cv.take<char>(a > b ? a : b);
+    if (bytes) *bytes = cv.used;
+    return w;
+}
+
+bool decay_tile(int32_t M, int32_t Ci, int32_t Co, bool bf) {
+    return tile_available(M, Ci, Co) && !fused_backward_available(M, Ci, Co, bf);
+}
+
 DecayWs carve_decay(void *base, int32_t n, int64_t nnz, int32_t M, int32_t Ci, int32_t Co,
                     size_t *bytes) {
     Carver cv(base);
@@ -514,6 +632,10 @@ extern "C" size_t sbc_decay_gradient_workspace_size(int32_t n, int64_t nnz_bound
                                                     sbc_dtype dtype) {
     if (n < 0 || nnz_bound < 0 || M <= 0 || C_in <= 0 || C_out <= 0) return 0;
     size_t bytes = 0;
+    if (decay_tile(M, C_in, C_out, dtype == SBC_BF16)) {
+        carve_decay_tile(nullptr, n, M, C_in, C_out, &bytes);
+        return bytes;
+    }
     carve_decay(nullptr, n, nnz_bound, M, C_in, C_out, &bytes);
     // the fused D-route: its own workspace, then dW'
     const size_t fused = fused_workspace_bytes(M, C_in, C_out, n, nnz_bound) +
@@ -544,7 +666,21 @@ extern "C" sbc_status sbc_conv_decay_gradient(const sbc_csr *csr, const sbc_csc 
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_decay_gradient_workspace_size()");
     if (n == 0) return fill_i32(reinterpret_cast<int32_t *>(dlambda), 0, M, stream);
     float *dWp;
-    if (csc && fused_backward_available(M, C_in, C_out, bf)) {
+    if (decay_tile(M, C_in, C_out, bf)) {
+        const DecayTileWs ws = carve_decay_tile(workspace, n, M, C_in, C_out, nullptr);
+        KGeo g;
+        SBC_TRY(make_kgeo(csr, nullptr, geometry, ws.packed, stream, &g));
+        dWp = ws.dWp;
+        const TilePattern rows{n, csr->row_ptr, csr->col_idx, nullptr, false};
+        if (csc)
+            SBC_TRY(tile_weight_gradient(
+                TilePattern{csc->n_cols, csc->col_ptr, csc->row_idx, nullptr, true}, nullptr, g,
+                kDecayDerivMode, M, F, dY, bf, C_in, C_out, dWp, ws.part, stream,
+                "decay_tile_dw"));
+        else
+            SBC_TRY(tile_weight_gradient(rows, nullptr, g, kDecayDerivMode, M, dY, F, bf, C_in,
+                                         C_out, dWp, ws.part, stream, "decay_tile_dw"));
+    } else if (csc && fused_backward_available(M, C_in, C_out, bf)) {
         // D' = N'^T dY gathered with the derivative values, dW' = F^T D' (dF skipped)
         const int32_t np = n > csr->n_cols ? n : csr->n_cols;
         dWp = reinterpret_cast<float *>(static_cast<char *>(workspace) +

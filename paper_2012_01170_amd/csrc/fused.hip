@@ -4,16 +4,7 @@
 // coordinates (the paper computes them on the accelerator from the neighbour
 // indices), or read from a materialised [E, M] array.
 //
-// Forward, one block per tile of TR output rows:
-//   gather   G[r, m*C_in + c] = sum_e v[e, m] F[j(e), c] into LDS.  The
-//            wave's edges are staged 64 at a time (index and basis values,
-//            one edge per lane) in LDS; every row is owned by LPR lanes that
-//            accumulate M x VEC values while walking the row's edges, loading
-//            VEC contiguous channels of F[j] per edge (16-byte loads);
-//   contract Y_tile = G_tile W on the matrix cores (float32: 16x16x4 f32
-//            MFMA with W read from L2; bf16: G rounded to bf16 in LDS and
-//            16x16x32 bf16 MFMA against a [C_out, M*C_in] copy of W).
-// Forward for narrow inputs (C_in <= 32, or 64 in bf16), persistent blocks of 8 waves: each
+// Forward, for narrow inputs (C_in <= 32, or 64 in bf16), persistent blocks of 8 waves: each
 //            wave owns 16-row tiles and keeps G in registers as the MFMA A
 //            operand; W stays in LDS for the life of the block.  A row's four
 //            lanes take four edges per step, with the next step's neighbour
@@ -35,14 +26,13 @@
 
 #include "basis.hpp"
 #include "common.hpp"
+#include "edge_basis.hpp"
 #include "fused.hpp"
+#include "split.hpp"
 #include "spmm.hpp"
 
 namespace sbc {
 namespace {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -69,78 +59,11 @@ __device__ __forceinline__ bf16x8 lds_column8(const uint16_t *p, int s) {
     return __builtin_bit_cast(bf16x8, r);
 }
 
-// ---------------------------------------------------------------- geometry
-// Geometry as the fused kernels read it: the caller's point coordinates, and
-// for event streams a packed copy (px, py, t, 0) per event, so that one
-// 16-byte load brings all three coordinates of an edge's far end (three
-// separate arrays would cost three cache lines per edge).
-struct KGeo {
-    double inv_r;
-    float inv_tau;
-    int32_t nnz;  // edge bound of the pattern: row extents are clamped to [0, nnz]
-    const float *x_in, *x_out;
-    const int4 *ev;
-    const float *decays;  // learned-decay rates [8, M / 8]
-};
-
-// Basis mode of the fused kernels for the derivatives of the learned-decay
-// basis with respect to its rates (the decay gradient's D-route pass).
-constexpr int kDecayDerivMode = 16;
-
-// Basis mode of the backward for the fixed-decay event basis when the
-// gathered rows, the packed events or the pattern arrays pass 4 GiB: the
-// generic gather (64-bit addressing) instead of the one-hot gather, whose
-// loads take 32-bit byte offsets from their arrays' bases.
-constexpr int kEvent8WideMode = 17;
-// The same for the learned-decay basis and its derivatives (M / 8 values per
-// edge), whose in-place gather takes 32-bit byte offsets too.
-constexpr int kDecaysWideMode = 18;
-constexpr int kDecayDerivWideMode = 19;
-
 __global__ void pack_events_kernel(const int32_t *__restrict__ px, const int32_t *__restrict__ py,
                                    const int32_t *__restrict__ t, int32_t n,
                                    int4 *__restrict__ out) {
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
         out[i] = make_int4(px[i], py[i], t[i], 0);
-}
-
-// ---------------------------------------------------------------- basis per edge
-// kBasis: 0 = read v[ev, :], SBC_BASIS_MONO4 + 1, SBC_BASIS_MONO8 + 1, SBC_BASIS_EVENT8 + 1,
-// SBC_BASIS_EVENT_DECAYS + 1 (M / 8 rates per offset), kDecayDerivMode (their
-// derivatives with respect to the rates) (i = output index, j = input index
-// of the edge, ev = its CSR position).
-template <int M, int kBasis>
-__device__ __forceinline__ void edge_basis(const KGeo &g, const float *__restrict__ v,
-                                           int32_t i, int32_t j, int64_t ev, double inv_r,
-                                           float inv_tau, float *out) {
-    if constexpr (kBasis == 0) {
-#pragma unroll
-        for (int m = 0; m < M; ++m) out[m] = v[ev * M + m];
-    } else if constexpr (kBasis == SBC_BASIS_EVENT8 + 1 || kBasis == kEvent8WideMode) {
-        const int4 a = g.ev[i], b = g.ev[j];
-        const int k = event_index(a.x - b.x, a.y - b.y);
-        const float d = event_decay(a.z, b.z, inv_tau);
-#pragma unroll
-        for (int m = 0; m < M; ++m) out[m] = (m == k) ? d : 0.f;
-    } else if constexpr (kBasis == SBC_BASIS_EVENT_DECAYS + 1 || kBasis == kDecayDerivMode) {
-        // the same expression as the basis values kernel, so the values agree bitwise
-        constexpr int Mv = M / 8;
-        const int4 a = g.ev[i], b = g.ev[j];
-        const int k = event_index(a.x - b.x, a.y - b.y);
-        const float dt = (float)((int64_t)a.z - (int64_t)b.z);
-        float x[Mv];
-#pragma unroll
-        for (int q = 0; q < Mv; ++q) {
-            x[q] = k >= 0 ? expf(-g.decays[k * Mv + q] * dt) : 0.f;
-            if (kBasis == kDecayDerivMode) x[q] = -dt * x[q];
-        }
-#pragma unroll
-        for (int m = 0; m < M; ++m) out[m] = (m / Mv == k) ? x[m % Mv] : 0.f;
-    } else {
-        point_basis<M>(g.x_out[3 * (int64_t)i], g.x_out[3 * (int64_t)i + 1],
-                       g.x_out[3 * (int64_t)i + 2], g.x_in[3 * (int64_t)j],
-                       g.x_in[3 * (int64_t)j + 1], g.x_in[3 * (int64_t)j + 2], inv_r, out);
-    }
 }
 
 // Per-wave LDS stage of up to 64 edges: neighbour index and basis values,
@@ -154,30 +77,7 @@ struct EdgeStage {
     int32_t bounds[17];
 };
 
-// VEC contiguous channels of row `r` of X (float32 or bf16) as float32.
-template <int C, int VEC, bool kXbf>
-__device__ __forceinline__ void load_row_vec(const void *__restrict__ Xv, int32_t r, int cg,
-                                             float *f) {
-    if constexpr (kXbf) {
-        const uint4 raw = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(Xv) +
-                                                           (int64_t)r * C + cg * VEC);
-        const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            f[2 * k] = __uint_as_float(w4[k] << 16);
-            f[2 * k + 1] = __uint_as_float(w4[k] & 0xFFFF0000u);
-        }
-    } else {
-        const float4 raw = *reinterpret_cast<const float4 *>(static_cast<const float *>(Xv) +
-                                                             (int64_t)r * C + cg * VEC);
-        f[0] = raw.x;
-        f[1] = raw.y;
-        f[2] = raw.z;
-        f[3] = raw.w;
-    }
-}
-
-// The same 16 bytes kept as loaded (four registers for 8 bf16 or 4 float32
+// 16 bytes of a row of X (VEC contiguous channels) kept as loaded (four registers for 8 bf16 or 4 float32
 // channels), converted where they are used: twice the bf16 edges in flight
 // for the registers of the converted form.
 template <bool kXbf>
@@ -1176,24 +1076,6 @@ __device__ __forceinline__ void mfma_lds_x_global_bf16(const uint16_t *As,
     }
 }
 
-// Tile rows per block: 64 while the G tile fits 64 KiB; else 32, or 16 for
-// wide outputs (128 and more channels), where a block's contraction is long
-// enough that three smaller blocks per CU overlap gathers and contractions
-// better than two larger ones (measured: C_out 128 fp32 36 -> 32 us; C_out 64
-// fp32 stays at 32 rows, 42 -> 49 us with 16).
-constexpr int fwd_tile_rows(int K, int CO, bool bf) {
-    return (K * (bf ? 2 : 4) * 64 <= 65536) ? 64 : (CO >= 128 ? 16 : 32);
-}
-
-// Logical tile of physical block b of n: consecutive blocks are dispatched to
-// the 8 XCDs in turn, so this gives each XCD one contiguous range of tiles and
-// keeps the rows an XCD gathers local to its L2.
-__device__ __forceinline__ int32_t xcd_tile(int32_t b, int32_t n) {
-    const int32_t per = n / 8, rem = n % 8;
-    const int32_t x = b % 8, l = b / 8;
-    return x < rem ? x * (per + 1) + l : rem * (per + 1) + (x - rem) * per + l;
-}
-
 // First tile of XCD x's range when the persistent kernels split n_tiles tiles
 // of TR rows over X XCDs: the ranges hold equal shares of the work estimate
 // (edges + kRowCost per row, from the pattern's pointer array), so an XCD
@@ -1239,68 +1121,6 @@ __device__ __forceinline__ int32_t xcd_range_begin(int32_t x, int32_t X, int32_t
         return r < n_tiles ? r : n_tiles;
     }
     return hi;
-}
-
-// ================================================================ forward
-constexpr int kFwdWaves = 4;
-
-template <int M, int CI, int CO, int kBasis, bool kBf>
-__global__ void __launch_bounds__(kFwdWaves * 64, fwd_tile_rows(M * CI, CO, kBf) == 16 ? 3 : 2)
-    fwd_fused_kernel(int32_t n_out, const int32_t *__restrict__ row_ptr,
-                     const int32_t *__restrict__ col_idx, const float *__restrict__ v,
-                     KGeo g, const void *__restrict__ F, const void *__restrict__ Wop,
-                     float *__restrict__ Y) {
-    constexpr int NW = kFwdWaves;
-    constexpr int K = M * CI;
-    constexpr int TR = fwd_tile_rows(K, CO, kBf);
-    constexpr int S = K + (kBf ? 8 : 4);           // padded LDS row (elements)
-    constexpr int NRB = TR / 16, NCB = CO / 16;
-    static_assert(CO % 16 == 0 && CI % 4 == 0, "shape");
-    constexpr int NCBW = NCB < NW ? NCB : NW;      // column groups of waves
-    constexpr int NRG = NW / NCBW;                 // row groups of waves
-    static_assert(NCB % NCBW == 0 && NRB % NRG == 0, "tile split");
-    constexpr int WCB = NCB / NCBW, WRB = NRB / NRG;
-    constexpr int RPW = TR / NW;
-
-    using GT = typename std::conditional<kBf, uint16_t, float>::type;
-    __shared__ __attribute__((aligned(16))) GT Gs[TR * S];
-    __shared__ EdgeStage<M> stage[NW];
-
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int32_t row0 = xcd_tile(blockIdx.x, gridDim.x) * TR;
-    const double inv_r = g.inv_r;
-    const float inv_tau = g.inv_tau;
-
-    gather_rows<M, CI, kBasis, kBf, kBf, false, RPW, false>(
-        row0 + w * RPW, n_out, row_ptr, col_idx, nullptr, v, g, F, Gs, S, w * RPW, stage[w],
-        inv_r, inv_tau,
-        GatherAhead{load_bound<RPW>(row_ptr, n_out, row0 + w * RPW, g.nnz), 0, false},
-        -1);
-    __syncthreads();
-
-    const int wc = w % NCBW, wr = w / NCBW;
-    floatx4 acc[WRB][WCB];
-#pragma unroll
-    for (int u = 0; u < WRB; ++u)
-#pragma unroll
-        for (int t = 0; t < WCB; ++t) acc[u][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    if constexpr (!kBf)
-        mfma_lds_x_global_f32t<K, S, WRB, WCB, NCBW, NRG>(
-            Gs, static_cast<const float *>(Wop), wr, wc, acc);
-    else
-        mfma_lds_x_global_bf16<K, S, WRB, WCB, NCBW, NRG>(
-            Gs, static_cast<const uint16_t *>(Wop), wr, wc, acc);
-#pragma unroll
-    for (int u = 0; u < WRB; ++u)
-#pragma unroll
-        for (int t = 0; t < WCB; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int32_t row = row0 + 16 * (wr + NRG * u) + 4 * (lane >> 4) + r;
-                if (row < n_out) Y[(int64_t)row * CO + 16 * (wc + NCBW * t) + (lane & 15)] = acc[u][t][r];
-            }
 }
 
 // ================================================================ row order
@@ -2304,38 +2124,7 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// W [M, CI, CO] (float32 or bf16) -> bf16 copy with element (m, c, p) at m*s_m + c*s_c + p*s_p
-template <typename T>
-__global__ void w_to_bf16_kernel(const T *__restrict__ W, int32_t M, int32_t CI, int32_t CO,
-                                 int64_t s_m, int64_t s_c, int64_t s_p, uint16_t *__restrict__ out) {
-    const int64_t total = (int64_t)M * CI * CO;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p = (int32_t)(x % CO);
-        const int32_t c = (int32_t)((x / CO) % CI);
-        const int32_t m = (int32_t)(x / ((int64_t)CO * CI));
-        uint16_t b;
-        if constexpr (sizeof(T) == 2) b = W[x]; else b = f2bf(W[x]);
-        out[m * s_m + c * s_c + p * s_p] = b;
-    }
-}
-
-// W [M, CI, CO] float32 -> float32 copy with element (m, c, p) at m*s_m + c*s_c + p*s_p
-__global__ void w_perm_f32_kernel(const float *__restrict__ W, int32_t M, int32_t CI, int32_t CO,
-                                  int64_t s_m, int64_t s_c, int64_t s_p, float *__restrict__ out) {
-    const int64_t total = (int64_t)M * CI * CO;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p = (int32_t)(x % CO);
-        const int32_t c = (int32_t)((x / CO) % CI);
-        const int32_t m = (int32_t)(x / ((int64_t)CO * CI));
-        out[m * s_m + c * s_c + p * s_p] = W[x];
-    }
-}
-
 // ---------------------------------------------------------------- dispatch tables
-using FwdFn = void (*)(int32_t, const int32_t *, const int32_t *, const float *, KGeo,
-                       const void *, const void *, float *);
 using RegFn = void (*)(int32_t, int32_t, const int32_t *, const int32_t *, const float *,
                        KGeo, const void *, const void *, float *, const int32_t *);
 using BwdFn = void (*)(int32_t, int32_t, const int32_t *, const int32_t *, const int32_t *,
@@ -2346,27 +2135,6 @@ struct Shape {
     int M, CI, CO;
     bool bf;
 };
-
-template <int M, int CI, int CO, bool kBf>
-FwdFn fwd_for(int basis_mode) {
-    switch (basis_mode) {
-        case 0: return fwd_fused_kernel<M, CI, CO, 0, kBf>;
-        case SBC_BASIS_MONO4 + 1:
-            if constexpr (M == 4) return fwd_fused_kernel<M, CI, CO, SBC_BASIS_MONO4 + 1, kBf>;
-            return nullptr;
-        case SBC_BASIS_MONO8 + 1:
-            if constexpr (M == 8) return fwd_fused_kernel<M, CI, CO, SBC_BASIS_MONO8 + 1, kBf>;
-            return nullptr;
-        case SBC_BASIS_EVENT8 + 1:
-            if constexpr (M == 8) return fwd_fused_kernel<M, CI, CO, SBC_BASIS_EVENT8 + 1, kBf>;
-            return nullptr;
-        case SBC_BASIS_EVENT_DECAYS + 1:
-            if constexpr (M >= 16 && M % 8 == 0)
-                return fwd_fused_kernel<M, CI, CO, SBC_BASIS_EVENT_DECAYS + 1, kBf>;
-            return nullptr;
-    }
-    return nullptr;
-}
 
 template <int M, int CI, int CO, bool kBf>
 RegFn reg_for(int basis_mode) {
@@ -2437,16 +2205,13 @@ BwdFn bwd_for(int basis_mode) {
     return nullptr;
 }
 
-// Shapes with fused kernels: (M, C_in, C_out, bf16).  The backward keeps a
+// Shapes with fused kernels: (M, C_in, C_out, bf16).  Forward: the shapes of
+// the register-resident kernel, whose rows are narrow.  The backward keeps a
 // C_in x M*C_out partial of dW per block in registers, so its list is limited
-// to C_in * M * C_out <= 32768.
+// to C_in * M * C_out <= 32768.  Other shapes take the tile passes (tile.hpp).
 #define SBC_FWD_SHAPES(X) \
     X(16, 32, 32, false)  \
-    X(10, 64, 64, false)  \
-    X(4, 64, 64, false)   \
     X(4, 16, 32, false)   \
-    X(8, 64, 64, false)   \
-    X(8, 64, 128, false)  \
     X(8, 32, 32, false)   \
     X(8, 64, 64, true)    \
     X(8, 32, 32, true)
@@ -2458,14 +2223,6 @@ BwdFn bwd_for(int basis_mode) {
     X(8, 32, 32, false)   \
     X(8, 64, 64, true)    \
     X(8, 32, 32, true)
-
-FwdFn find_fwd(const Shape &s, int basis_mode) {
-#define SBC_X(m_, ci_, co_, bf_) \
-    if (s.M == m_ && s.CI == ci_ && s.CO == co_ && s.bf == bf_) return fwd_for<m_, ci_, co_, bf_>(basis_mode);
-    SBC_FWD_SHAPES(SBC_X)
-#undef SBC_X
-    return nullptr;
-}
 
 RegFn find_reg(const Shape &s, int basis_mode) {
 #define SBC_X(m_, ci_, co_, bf_) \
@@ -2496,35 +2253,12 @@ int basis_mode_of(const float *v, const sbc_geometry *g) {
     return v ? 0 : (int)g->basis + 1;
 }
 
-sbc_status launch_perm(const void *W, bool bf_in, bool bf_out, int32_t M, int32_t CI, int32_t CO,
-                       int64_t s_m, int64_t s_c, int64_t s_p, void *out, hipStream_t stream) {
-    const int64_t total = (int64_t)M * CI * CO;
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    if (bf_out) {
-        if (bf_in)
-            hipLaunchKernelGGL(w_to_bf16_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0,
-                               stream, static_cast<const uint16_t *>(W), M, CI, CO, s_m, s_c, s_p,
-                               static_cast<uint16_t *>(out));
-        else
-            hipLaunchKernelGGL(w_to_bf16_kernel<float>, dim3((unsigned)blocks), dim3(256), 0,
-                               stream, static_cast<const float *>(W), M, CI, CO, s_m, s_c, s_p,
-                               static_cast<uint16_t *>(out));
-    } else {
-        hipLaunchKernelGGL(w_perm_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
-                           static_cast<const float *>(W), M, CI, CO, s_m, s_c, s_p,
-                           static_cast<float *>(out));
-    }
-    SBC_LAUNCH_CHECK();
-    return SBC_OK;
-}
-
 }  // namespace
 
 // every listed shape has all basis variants of its M, so availability
 // depends on the shape only
 bool fused_forward_available(int32_t M, int32_t CI, int32_t CO, bool bf) {
-    return find_fwd(Shape{M, CI, CO, bf}, 0) != nullptr;
+    return find_reg(Shape{M, CI, CO, bf}, 0) != nullptr;
 }
 
 bool fused_backward_available(int32_t M, int32_t CI, int32_t CO, bool bf) {
@@ -2541,24 +2275,16 @@ size_t fused_workspace_bytes(int32_t M, int32_t CI, int32_t CO, int32_t n_points
            (M == 10 ? align_up((size_t)(nnz > 0 ? nnz : 0) * M * 4) : 0);
 }
 
-// The forward needs no dW partials: the weight copy, the packed events, the
-// row order of the register-resident forward and (M = 10) the basis values.
-size_t fused_forward_workspace_bytes(int32_t M, int32_t CI, int32_t CO, int32_t n_points,
-                                     int64_t nnz) {
+// The forward: the packed events and the row order.
+size_t fused_forward_workspace_bytes(int32_t n_points) {
     const size_t n = (size_t)(n_points > 0 ? n_points : 0);
-    return align_up((size_t)M * CI * CO * 4) + align_up(n * sizeof(int4)) +
-           align_up(n * sizeof(int32_t)) +
-           (M == 10 ? align_up((size_t)(nnz > 0 ? nnz : 0) * M * 4) : 0);
+    return align_up(n * sizeof(int4)) + align_up(n * sizeof(int32_t));
 }
 
-namespace {
-
-// Kernel geometry for a call: packs the event coordinates into the workspace
-// (after the weight copy and the dW partials) when the basis is evaluated
-// from an event stream.
-// ev_offset: where the packed events go in the workspace.
-sbc_status make_kgeo(const sbc_csr *csr, const float *v, const sbc_geometry *g, size_t ev_offset,
-                     void *ws, hipStream_t stream, KGeo *kg) {
+// Kernel geometry for a call; where the basis is evaluated from an event
+// stream, its coordinates are packed into `packed` (an int4 per event).
+sbc_status make_kgeo(const sbc_csr *csr, const float *v, const sbc_geometry *g, void *packed,
+                     hipStream_t stream, KGeo *kg) {
     *kg = KGeo{};
     kg->nnz = csr->nnz_bound > INT32_MAX ? INT32_MAX : (int32_t)csr->nnz_bound;
     if (v || !g) return SBC_OK;
@@ -2570,7 +2296,7 @@ sbc_status make_kgeo(const sbc_csr *csr, const float *v, const sbc_geometry *g, 
     if (g->basis == SBC_BASIS_EVENT8 || g->basis == SBC_BASIS_EVENT_DECAYS) {
         // event streams are in place: rows and columns index the same events
         const int32_t n = csr->n_cols > csr->n_rows ? csr->n_cols : csr->n_rows;
-        int4 *pk = reinterpret_cast<int4 *>(static_cast<char *>(ws) + ev_offset);
+        int4 *pk = static_cast<int4 *>(packed);
         if (n > 0) {
             int blocks = grid_for(n, 256);
             if (blocks > 2048) blocks = 2048;
@@ -2583,26 +2309,15 @@ sbc_status make_kgeo(const sbc_csr *csr, const float *v, const sbc_geometry *g, 
     return SBC_OK;
 }
 
-}  // namespace
-
 sbc_status fused_forward(const sbc_csr *csr, const float *v, const sbc_geometry *g, int32_t M,
                          const void *F, const void *W, bool bf, int32_t CI, int32_t CO, float *Y,
                          void *ws, hipStream_t stream) {
-    if (!v && g->basis == SBC_BASIS_WMONO10) {
-        // row-normalised values: materialised first, behind the other regions
-        const int32_t n = csr->n_cols > csr->n_rows ? csr->n_cols : csr->n_rows;
-        float *vm = reinterpret_cast<float *>(
-            static_cast<char *>(ws) + fused_forward_workspace_bytes(M, CI, CO, n, 0));
-        SBC_TRY(basis_eval_launch(csr, g, vm, stream));
-        v = vm;
-    }
-    FwdFn fn = find_fwd(Shape{M, CI, CO, bf}, basis_mode_of(v, g));
-    if (!fn) return fail(SBC_ERR_UNSUPPORTED, "no fused forward for this shape");
+    RegFn rf = find_reg(Shape{M, CI, CO, bf}, basis_mode_of(v, g));
+    if (!rf) return fail(SBC_ERR_UNSUPPORTED, "no fused forward for this shape");
     if (csr->n_rows == 0) return SBC_OK;
     KGeo gr;
-    // layout: [W copy][packed events][row order][M = 10: basis values]
-    SBC_TRY(make_kgeo(csr, v, g, align_up((size_t)M * CI * CO * 4), ws, stream, &gr));
-    RegFn rf = find_reg(Shape{M, CI, CO, bf}, basis_mode_of(v, g));
+    // layout: [packed events][row order]
+    SBC_TRY(make_kgeo(csr, v, g, ws, stream, &gr));
     // the fixed-decay event basis on rows of 32 float32 channels: the one-hot
     // forward, whose loads take 32-bit byte offsets (F rows, packed events and
     // the pattern's indices under 4 GiB; else, or with SBC_EVENT8_WIDE_PATH=1,
@@ -2617,52 +2332,38 @@ sbc_status fused_forward(const sbc_csr *csr, const float *v, const sbc_geometry 
             csr->nnz_bound * 4 >= lim || csr->nnz_bound < 1 || (force && force[0] == '1'))
             onehot = false;
     }
-    if (rf || onehot) {
-        const int32_t n_tiles = (csr->n_rows + 15) / 16;
-        const int32_t np = csr->n_cols > csr->n_rows ? csr->n_cols : csr->n_rows;
-        int32_t *order = reinterpret_cast<int32_t *>(
-            static_cast<char *>(ws) + align_up((size_t)M * CI * CO * 4) +
-            align_up((size_t)np * sizeof(int4)));
-        hipLaunchKernelGGL(row_order_kernel,
-                           dim3(grid_for(csr->n_rows, kOrderWindow * (kOrderThreads / 64))),
-                           dim3(kOrderThreads), 0, stream, csr->n_rows, csr->row_ptr, gr.nnz,
-                           order);
-        SBC_LAUNCH_CHECK();
-        if (onehot) {
-            // one block per CU (its LDS holds W and the eight waves' G slots)
-            int blocks = (n_tiles + kOhWaves - 1) / kOhWaves;
-            if (blocks > device_cus()) blocks = device_cus();
-            trace_before("fwd_fused", stream);
-            hipLaunchKernelGGL((fwd_onehot_kernel<32, 32>), dim3(blocks), dim3(kOhWaves * 64), 0,
-                               stream, csr->n_rows, n_tiles, csr->row_ptr, csr->col_idx, gr,
-                               static_cast<const float *>(F), static_cast<const float *>(W), Y,
-                               order);
-            SBC_LAUNCH_CHECK();
-            trace_after("fwd_fused", stream);
-            return SBC_OK;
-        }
-        int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(rf),
-                                                         kRegWaves * 64, 0) != hipSuccess ||
-            per_cu < 1)
-            per_cu = 1;
-        int blocks = (n_tiles + kRegWaves - 1) / kRegWaves;
-        if (blocks > device_cus() * per_cu) blocks = device_cus() * per_cu;
+    const int32_t n_tiles = (csr->n_rows + 15) / 16;
+    const int32_t np = csr->n_cols > csr->n_rows ? csr->n_cols : csr->n_rows;
+    int32_t *order = reinterpret_cast<int32_t *>(
+        static_cast<char *>(ws) + align_up((size_t)np * sizeof(int4)));
+    hipLaunchKernelGGL(row_order_kernel,
+                       dim3(grid_for(csr->n_rows, kOrderWindow * (kOrderThreads / 64))),
+                       dim3(kOrderThreads), 0, stream, csr->n_rows, csr->row_ptr, gr.nnz,
+                       order);
+    SBC_LAUNCH_CHECK();
+    if (onehot) {
+        // one block per CU (its LDS holds W and the eight waves' G slots)
+        int blocks = (n_tiles + kOhWaves - 1) / kOhWaves;
+        if (blocks > device_cus()) blocks = device_cus();
         trace_before("fwd_fused", stream);
-        hipLaunchKernelGGL(rf, dim3(blocks), dim3(kRegWaves * 64), 0, stream, csr->n_rows,
-                           n_tiles, csr->row_ptr, csr->col_idx, v, gr, F, W, Y, order);
+        hipLaunchKernelGGL((fwd_onehot_kernel<32, 32>), dim3(blocks), dim3(kOhWaves * 64), 0,
+                           stream, csr->n_rows, n_tiles, csr->row_ptr, csr->col_idx, gr,
+                           static_cast<const float *>(F), static_cast<const float *>(W), Y,
+                           order);
         SBC_LAUNCH_CHECK();
         trace_after("fwd_fused", stream);
         return SBC_OK;
     }
-    // W transposed, [CO, K]: element (m, c, p) at p*K + m*CI + c (float32 or bf16)
-    SBC_TRY(launch_perm(W, bf, bf, M, CI, CO, CI, 1, (int64_t)M * CI, ws, stream));
-    const void *Wop = ws;
-    const int K = M * CI;
-    const int TR = fwd_tile_rows(K, CO, bf);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(rf),
+                                                     kRegWaves * 64, 0) != hipSuccess ||
+        per_cu < 1)
+        per_cu = 1;
+    int blocks = (n_tiles + kRegWaves - 1) / kRegWaves;
+    if (blocks > device_cus() * per_cu) blocks = device_cus() * per_cu;
     trace_before("fwd_fused", stream);
-    hipLaunchKernelGGL(fn, dim3(grid_for(csr->n_rows, TR)), dim3(kFwdWaves * 64), 0, stream,
-                       csr->n_rows, csr->row_ptr, csr->col_idx, v, gr, F, Wop, Y);
+    hipLaunchKernelGGL(rf, dim3(blocks), dim3(kRegWaves * 64), 0, stream, csr->n_rows,
+                       n_tiles, csr->row_ptr, csr->col_idx, v, gr, F, W, Y, order);
     SBC_LAUNCH_CHECK();
     trace_after("fwd_fused", stream);
     return SBC_OK;
@@ -2715,9 +2416,9 @@ sbc_status fused_backward(const sbc_csr *csr, const sbc_csc *csc, const float *v
     KGeo gg;
     // layout: [W copy][dW partials][packed events]
     SBC_TRY(make_kgeo(csr, v, g,
-                      align_up((size_t)M * CI * CO * 4) +
+                      base + align_up((size_t)M * CI * CO * 4) +
                           align_up((size_t)kMaxBlocksBwd * (size_t)CI * M * CO * 4),
-                      ws, stream, &gg));
+                      stream, &gg));
     if (n_in > 0 && (dF || dW)) {
         trace_before(decay_derivative ? "decay_fused" : "bwd_fused", stream);
         hipLaunchKernelGGL(fn, dim3(blocks), dim3(nw * 64), 0, stream, n_in, n_tiles, csc->col_ptr,

@@ -22,6 +22,9 @@ sbc_status check_csr(const sbc_csr *csr);
 sbc_status check_geometry(const sbc_geometry *g, int32_t n_rows, int32_t n_cols);
 sbc_status basis_eval_launch(const sbc_csr *csr, const sbc_geometry *g, float *v,
                              hipStream_t stream);
+// the weighted basis's weight sums W_i [n_rows]
+sbc_status weight_sums_launch(const sbc_csr *csr, const sbc_geometry *g, double *wsum,
+                              hipStream_t stream);
 // the learned-decay basis's derivatives with respect to the rates (CSR order)
 sbc_status decay_derivative_launch(const sbc_csr *csr, const sbc_geometry *g, float *v,
                                    hipStream_t stream);

@@ -1,0 +1,54 @@
+// tile_dw_kernel for every basis size.
+#include "tile_launch.hpp"
+
+namespace sbc {
+
+template <int M, bool kXbf, bool kCompact, int NPB>
+static void launch_one(const TileDwArgs &a, hipStream_t s) {
+    using T = DwShape<M, NPB, kCompact>;
+    const int32_t slices = (a.CQ + kTileCS - 1) / kTileCS;
+    const int32_t chunks = (a.CP + 16 * NPB - 1) / (16 * NPB);
+    hipLaunchKernelGGL((tile_dw_kernel<M, kXbf, kCompact, NPB>),
+                       dim3((unsigned)a.splits, (unsigned)(slices * chunks)), dim3(kTileThreads),
+                       0, s, a.p, a.v, a.g, a.mode, a.P, a.CP, a.Q, a.CQ,
+                       (a.p.n_rows + T::TR - 1) / T::TR, a.part);
+}
+
+template <int M, bool kCompact>
+static void launch_p(bool bf16, const TileDwArgs &a, hipStream_t s) {
+    if constexpr (M < 16) {
+        if (dw_npb(M, a.CP) == 4) {
+            if (bf16) launch_one<M, true, kCompact, 4>(a, s);
+            else launch_one<M, false, kCompact, 4>(a, s);
+            return;
+        }
+    }
+    if (bf16) launch_one<M, true, kCompact, 2>(a, s);
+    else launch_one<M, false, kCompact, 2>(a, s);
+}
+
+template <int M>
+static void launch_m(bool bf16, const TileDwArgs &a, hipStream_t s) {
+    if constexpr (M == 8 || M == 10) {
+        if (a.mode == SBC_BASIS_MONO8 + 1 || a.mode == SBC_BASIS_WMONO10 + 1) {
+            launch_p<M, true>(bf16, a, s);
+            return;
+        }
+    }
+    launch_p<M, false>(bf16, a, s);
+}
+
+sbc_status launch_dw(int32_t M, bool bf16, const TileDwArgs &a, hipStream_t s) {
+    switch (M) {
+        case 4: launch_m<4>(bf16, a, s); break;
+        case 8: launch_m<8>(bf16, a, s); break;
+        case 10: launch_m<10>(bf16, a, s); break;
+        case 16: launch_m<16>(bf16, a, s); break;
+        case 24: launch_m<24>(bf16, a, s); break;
+        default: launch_m<32>(bf16, a, s); break;
+    }
+    SBC_LAUNCH_CHECK();
+    return SBC_OK;
+}
+
+}  // namespace sbc
