@@ -4,26 +4,33 @@
 
 namespace sbc {
 
-template <int M, bool kCompact>
+template <int M, StageKind kKind>
 static void launch_p(bool bf16, const TileContractArgs &a, hipStream_t s) {
     if (a.tr == 64) {
-        if (bf16) launch_contract<M, true, kCompact, 64>(a, s);
-        else launch_contract<M, false, kCompact, 64>(a, s);
+        if (bf16) launch_contract<M, true, kKind, 64>(a, s);
+        else launch_contract<M, false, kKind, 64>(a, s);
     } else {
-        if (bf16) launch_contract<M, true, kCompact, 32>(a, s);
-        else launch_contract<M, false, kCompact, 32>(a, s);
+        if (bf16) launch_contract<M, true, kKind, 32>(a, s);
+        else launch_contract<M, false, kKind, 32>(a, s);
     }
 }
 
 template <int M>
 static void launch_m(bool bf16, const TileContractArgs &a, hipStream_t s) {
+    const StageKind kind = stage_kind(M, a.mode);
     if constexpr (M == 8 || M == 10) {
-        if (a.mode == SBC_BASIS_MONO8 + 1 || a.mode == SBC_BASIS_WMONO10 + 1) {
-            launch_p<M, true>(bf16, a, s);
+        if (kind == kCompact) {
+            launch_p<M, kCompact>(bf16, a, s);
             return;
         }
     }
-    launch_p<M, false>(bf16, a, s);
+    if constexpr (M == 8) {
+        if (kind == kEvents) {
+            launch_p<M, kEvents>(bf16, a, s);
+            return;
+        }
+    }
+    launch_p<M, kValues>(bf16, a, s);
 }
 
 sbc_status launch_contract_4_8_10(int32_t M, bool bf16, const TileContractArgs &a, hipStream_t s) {

@@ -5,8 +5,13 @@ namespace sbc {
 
 template <int M>
 static void launch_m(bool bf16, const TileContractArgs &a, hipStream_t s) {
-    if (bf16) launch_contract<M, true, false, 32>(a, s);
-    else launch_contract<M, false, false, 32>(a, s);
+    if (stage_kind(M, a.mode) == kEvents) {
+        if (bf16) launch_contract<M, true, kEvents, 32>(a, s);
+        else launch_contract<M, false, kEvents, 32>(a, s);
+    } else {
+        if (bf16) launch_contract<M, true, kValues, 32>(a, s);
+        else launch_contract<M, false, kValues, 32>(a, s);
+    }
 }
 
 sbc_status launch_contract_16_24_32(int32_t M, bool bf16, const TileContractArgs &a,

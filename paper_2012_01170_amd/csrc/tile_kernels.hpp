@@ -33,31 +33,52 @@ __device__ __forceinline__ void tile_wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// edge_basis by a run-time mode (wave-uniform; the point bases of M = 8 and 10
-// are staged by compact_entry)
+// What the stage holds of an entry, beside its other end:
+//   kValues   its M basis values;
+//   kCompact  point bases of M = 8 and 10: u = (x'_i - x_j) / r and the weight;
+//   kEvents   event bases: the offset index and the M / 8 decays (or their
+//             derivatives) of that offset, the only values that are not zero.
+// The shorter forms leave room for all entries of a wave's rows, which are then
+// staged once for all slices.
+enum StageKind { kValues = 0, kCompact = 1, kEvents = 2 };
+
+// Stage kind of a basis mode.
+__host__ __device__ constexpr StageKind stage_kind(int32_t M, int mode) {
+    return mode == SBC_BASIS_MONO8 + 1 || mode == SBC_BASIS_WMONO10 + 1 ? kCompact
+           : mode == 0 || M == 4                                        ? kValues
+                                                                        : kEvents;
+}
+
+// words of a staged entry (16-byte entries stay aligned)
+template <int M, StageKind kKind>
+constexpr int stage_words() {
+    return kKind == kCompact ? 4 : kKind == kEvents ? 1 + M / 8 : M;
+}
+
+// Offset index (8: none, a same-pixel edge) and decays of an event edge, in the
+// expressions of the basis values kernel.
 template <int M>
-__device__ __forceinline__ void edge_basis_of(int mode, const KGeo &g, const float *v, int32_t i,
-                                              int32_t j, int64_t ev, float *out) {
-    if (mode == 0) {
-        edge_basis<M, 0>(g, v, i, j, ev, g.inv_r, g.inv_tau, out);
-    } else if constexpr (M == 4) {
-        edge_basis<M, SBC_BASIS_MONO4 + 1>(g, v, i, j, ev, g.inv_r, g.inv_tau, out);
-    } else if constexpr (M == 8) {
-        edge_basis<M, SBC_BASIS_EVENT8 + 1>(g, v, i, j, ev, g.inv_r, g.inv_tau, out);
-    } else if constexpr (M >= 16) {
-        if (mode == SBC_BASIS_EVENT_DECAYS + 1)
-            edge_basis<M, SBC_BASIS_EVENT_DECAYS + 1>(g, v, i, j, ev, g.inv_r, g.inv_tau, out);
-        else
-            edge_basis<M, kDecayDerivMode>(g, v, i, j, ev, g.inv_r, g.inv_tau, out);
+__device__ __forceinline__ void event_entry(int mode, const KGeo &g, int32_t i, int32_t j,
+                                            float *out) {
+    constexpr int Mv = M / 8;
+    const int4 a = g.ev[i], b = g.ev[j];
+    const int k = event_index(a.x - b.x, a.y - b.y);
+    out[0] = __int_as_float(k >= 0 ? k : 8);
+    if constexpr (Mv == 1) {
+        out[1] = event_decay(a.z, b.z, g.inv_tau);
+    } else {
+        const float dt = (float)((int64_t)a.z - (int64_t)b.z);
+#pragma unroll
+        for (int q = 0; q < Mv; ++q) {
+            const float x = expf(-g.decays[(k >= 0 ? k : 0) * Mv + q] * dt);
+            out[1 + q] = mode == kDecayDerivMode ? -dt * x : x;
+        }
     }
 }
 
-// The point bases of M = 8 and 10 are staged as u = (x'_i - x_j) / r and the
-// weight, float64 rounded once; their monomials are formed where they are used
-// (three float32 roundings at most).  20 bytes an entry instead of 36 or 44
-// leave room for all entries of a wave's rows, which are then staged once for
-// all slices.  Weight: (1 - |u|^2)^2 (M = 8), (1 - |u|) / W_i (M = 10; 0 where
-// W_i = 0).
+// u and the weight of an edge of a point basis, float64 rounded once (the
+// monomials are formed where they are used: three float32 roundings at most).
+// Weight: (1 - |u|^2)^2 (M = 8), (1 - |u|) / W_i (M = 10; 0 where W_i = 0).
 template <int M>
 __device__ __forceinline__ float4 compact_entry(const KGeo &g, int32_t i, int32_t j) {
     const float *q = g.x_out + 3 * (int64_t)i, *s = g.x_in + 3 * (int64_t)j;
@@ -77,10 +98,10 @@ __device__ __forceinline__ float4 compact_entry(const KGeo &g, int32_t i, int32_
 }
 
 // Entries a wave stages at once (entry SW weighs nothing: the slots past a
-// row's end read it).  kCompact: u and the weight, else the M basis values.
-template <int M, int SW, bool kCompact>
+// row's end read it).
+template <int M, int SW, StageKind kKind>
 struct TileStage {
-    static constexpr int NV = kCompact ? 4 : M;
+    static constexpr int NV = stage_words<M, kKind>();
     float v[SW + 1][NV];
     int32_t nb[SW + 1];
 };
@@ -93,7 +114,7 @@ struct TileStage {
 // products run on the matrix cores as 16 independent 4 x 4 outer products (an
 // entry's 4 basis functions x 4 lanes' channels; float32): as plain FMAs, M
 // per channel and entry, they kept the vector ALU busy longer than the loads.
-template <int M, bool kXbf, bool kCompact, int RPW, int SW, int U_>
+template <int M, bool kXbf, StageKind kKind, int RPW, int SW, int U_>
 struct TileGather {
     static constexpr int LPR = 64 / RPW;
     static_assert(LPR == 4 || LPR == 8, "a row is 4 or 8 lanes");
@@ -103,7 +124,7 @@ struct TileGather {
     static constexpr int VT = NL * VEC;      // channels per lane
     static constexpr int U = U_;             // entries of a row loaded together
     static constexpr int MG = (M + 3) / 4;   // groups of 4 basis functions
-    using Stage = TileStage<M, SW, kCompact>;
+    using Stage = TileStage<M, SW, kKind>;
     // sums of basis function 4 g + r and the lane's channel k: [g][k][r]
     using Acc = floatx4[MG][VT];
     using Raw = typename std::conditional<
@@ -128,7 +149,7 @@ struct TileGather {
         lane = threadIdx.x & 63;
         rl = lane / LPR;
         piece = lane % LPR;
-        if (lane < Stage::NV) st.v[SW][lane] = 0.f;
+        if (lane < Stage::NV) st.v[SW][lane] = kKind == kEvents && lane == 0 ? __int_as_float(8) : 0.f;
     }
 
     // row bounds of the wave's rows (clamped into [0, nnz])
@@ -167,14 +188,20 @@ struct TileGather {
                 // (slots without an entry read a row the wave reads anyway: one
                 // row for all waves made its cache line the bottleneck)
                 if (e == c0) st.nb[SW] = other;
-                if constexpr (kCompact) {
+                if constexpr (kKind == kCompact) {
                     *reinterpret_cast<float4 *>(st.v[e - c0]) = compact_entry<M>(g, i, j);
                 } else {
-                    const int64_t ev = mode == 0 ? (p.perm ? (int64_t)p.perm[e] : (int64_t)e) : 0;
-                    float b[M];
-                    edge_basis_of<M>(mode, g, v, i, j, ev, b);
+                    float b[Stage::NV];
+                    if constexpr (kKind == kEvents) {
+                        event_entry<M>(mode, g, i, j, b);
+                    } else if (mode == 0) {
+                        edge_basis<M, 0>(g, v, i, j, p.perm ? (int64_t)p.perm[e] : (int64_t)e,
+                                         g.inv_r, g.inv_tau, b);
+                    } else if constexpr (M == 4) {
+                        edge_basis<M, SBC_BASIS_MONO4 + 1>(g, v, i, j, 0, g.inv_r, g.inv_tau, b);
+                    }
 #pragma unroll
-                    for (int m = 0; m < M; ++m) st.v[e - c0][m] = b[m];
+                    for (int m = 0; m < Stage::NV; ++m) st.v[e - c0][m] = b[m];
                 }
             }
         }
@@ -184,11 +211,31 @@ struct TileGather {
     // this lane's basis functions (4 g + lane % 4) of a staged entry
     __device__ __forceinline__ void values(int32_t at, float (&w)[MG]) const {
         const int t = lane & 3;
-        if constexpr (!kCompact) {
+        if constexpr (kKind == kValues) {
 #pragma unroll
             for (int q = 0; q < MG; ++q) {
                 if constexpr (M % 4 == 0) w[q] = st.v[at][4 * q + t];
                 else w[q] = 4 * q + t < M ? st.v[at][4 * q + t < M ? 4 * q + t : 0] : 0.f;
+            }
+        } else if constexpr (kKind == kEvents) {
+            constexpr int Mv = M / 8;
+            const int k = __float_as_int(st.v[at][0]);
+            if constexpr (4 % Mv == 0) {  // the lane's decay is the same in every group
+                const float d = st.v[at][1 + t % Mv];
+#pragma unroll
+                for (int q = 0; q < MG; ++q) w[q] = (4 * q + t) / Mv == k ? d : 0.f;
+            } else {
+                float d[Mv];
+#pragma unroll
+                for (int q = 0; q < Mv; ++q) d[q] = st.v[at][1 + q];
+#pragma unroll
+                for (int q = 0; q < MG; ++q) {
+                    const int m = 4 * q + t, r = m % Mv;
+                    float x = d[0];
+#pragma unroll
+                    for (int z = 1; z < Mv; ++z) x = r == z ? d[z] : x;
+                    w[q] = m / Mv == k ? x : 0.f;
+                }
             }
         } else {
             const float4 e = *reinterpret_cast<const float4 *>(st.v[at]);
@@ -389,9 +436,9 @@ constexpr int kTileThreads = 256;
 constexpr int kTileWaves = 4;
 
 // Stage entries per wave that `bytes` of LDS hold (at most 384).
-template <int M, bool kCompact>
+template <int M, StageKind kKind>
 constexpr int stage_entries(int bytes) {
-    const int n = (bytes / (kTileWaves * 4 * ((kCompact ? 4 : M) + 1)) - 1) / 32 * 32;
+    const int n = (bytes / (kTileWaves * 4 * (stage_words<M, kKind>() + 1)) - 1) / 32 * 32;
     return n > 384 ? 384 : n;
 }
 
@@ -411,11 +458,11 @@ constexpr int kTileU = tile_u<M, kXbf, RPW, kept>();
 // Tiles of TR rows of the contraction.  Four basis functions' 32 channels are
 // in LDS at a time (128 columns, TR x 816 bytes for the three parts); the
 // stage fills what two blocks a CU leave.
-template <int M, int TR, bool kCompact>
+template <int M, int TR, StageKind kKind>
 struct TileShape {
     static constexpr int RPW = TR / kTileWaves;
     static constexpr int S = 128 + 8;  // 4 mod 64 dwords: 16 rows' b128 reads on distinct banks
-    static constexpr int SW = stage_entries<M, kCompact>(81920 - 3 * TR * S * 2);
+    static constexpr int SW = stage_entries<M, kKind>(81920 - 3 * TR * S * 2);
     static_assert(SW >= 64, "a stage of at least 64 entries");
 };
 
@@ -424,18 +471,18 @@ struct TileShape {
 // columns apart) and WRB row blocks.  B comes as fragments (tile_frag_kernel)
 // straight from L2, 6 M C N bytes for every TR rows, hence 64 rows where they
 // fill the chip.  The second block of the CU covers this one's gather.
-template <int M, bool kXbf, bool kCompact, int TR, int NCBW, int WCB>
+template <int M, bool kXbf, StageKind kKind, int TR, int NCBW, int WCB>
 __global__ void __launch_bounds__(kTileThreads, 2)
     tile_contract_kernel(TilePattern p, const float *__restrict__ v, KGeo g, int mode,
                          const void *__restrict__ X, int32_t C,
                          const uint16_t *__restrict__ frag, int32_t N, float *__restrict__ out) {
-    using T = TileShape<M, TR, kCompact>;
+    using T = TileShape<M, TR, kKind>;
     constexpr int NRG = kTileWaves / NCBW;
     constexpr int WRB = TR / 16 / NRG;
     constexpr int NB = kXbf ? 1 : 3;
     // entries loaded together: as many as the accumulators leave registers for
     constexpr int U = kTileU<M, kXbf, TR / kTileWaves, WRB * WCB * 4>;
-    using Gather = TileGather<M, kXbf, kCompact, T::RPW, T::SW, U>;
+    using Gather = TileGather<M, kXbf, kKind, T::RPW, T::SW, U>;
     __shared__ __attribute__((aligned(16))) uint16_t planes[3][TR][T::S];
     __shared__ __attribute__((aligned(16))) typename Gather::Stage stage[kTileWaves];
 
@@ -545,28 +592,28 @@ __device__ __forceinline__ bf16x8 lds_rows8(const uint16_t *p) {
 
 // One k-step of 32 rows per tile; four basis functions' 32 channels (8 column
 // blocks, two per wave) are in LDS at a time.
-template <int M, int NPB, bool kCompact>
+template <int M, int NPB, StageKind kKind>
 struct DwShape {
     static constexpr int TR = 32;
     static constexpr int RPW = TR / kTileWaves;
     static constexpr int MG = (M + 3) / 4;
     static constexpr int S = 128 + 16;        // 8 mod 64 dwords: the four rows of a
     static constexpr int SP = NPB * 16 + 16;  // transposing read on distinct banks
-    static constexpr int SW = stage_entries<M, kCompact>(81920 - 3 * TR * (S + SP) * 2);
+    static constexpr int SW = stage_entries<M, kKind>(81920 - 3 * TR * (S + SP) * 2);
     static_assert(SW >= 32, "a stage of at least 32 entries");
 };
 
 // Block (x, y): split x of the row tiles, slice y % slices of Q's channels and
 // chunk y / slices (16 NPB channels) of P's.  part[x][c_P][m][c_Q].
-template <int M, bool kXbf, bool kCompact, int NPB>
+template <int M, bool kXbf, StageKind kKind, int NPB>
 __global__ void __launch_bounds__(kTileThreads, (M <= 16 ? 2 : 1))
     tile_dw_kernel(TilePattern p, const float *__restrict__ v, KGeo g, int mode,
                    const void *__restrict__ P, int32_t CP, const void *__restrict__ Q, int32_t CQ,
                    int32_t n_tiles, float *__restrict__ part) {
-    using T = DwShape<M, NPB, kCompact>;
+    using T = DwShape<M, NPB, kKind>;
     constexpr int NA = kXbf ? 1 : 3;  // parts of P
     constexpr int U = kTileU<M, kXbf, T::RPW, (M <= 16 ? T::MG * 2 * NPB * 4 : 64)>;
-    using Gather = TileGather<M, kXbf, kCompact, T::RPW, T::SW, U>;
+    using Gather = TileGather<M, kXbf, kKind, T::RPW, T::SW, U>;
     __shared__ __attribute__((aligned(16))) uint16_t dpl[3][T::TR][T::S];
     __shared__ __attribute__((aligned(16))) uint16_t ppl[NA][T::TR][T::SP];
     __shared__ __attribute__((aligned(16))) typename Gather::Stage stage[kTileWaves];

@@ -6,12 +6,12 @@
 
 namespace sbc {
 
-template <int M, bool kXbf, bool kCompact, int TR>
+template <int M, bool kXbf, StageKind kKind, int TR>
 void launch_contract(const TileContractArgs &a, hipStream_t s) {
     const int32_t ncb = (a.N + 15) / 16;
     const unsigned tiles = (unsigned)grid_for(a.p.n_rows, TR);
 #define SBC_TILE(NCBW, WCB)                                                                      \
-    hipLaunchKernelGGL((tile_contract_kernel<M, kXbf, kCompact, TR, NCBW, WCB>),                            \
+    hipLaunchKernelGGL((tile_contract_kernel<M, kXbf, kKind, TR, NCBW, WCB>),                            \
                        dim3(tiles, (unsigned)((ncb + NCBW * WCB - 1) / (NCBW * WCB))),            \
                        dim3(kTileThreads), 0, s, a.p, a.v, a.g, a.mode, a.X, a.C, a.frag, a.N,    \
                        a.out)
