@@ -79,6 +79,8 @@ TRACE_NAME = {"bwd_ws_kernel": "bwd_fused",
               "fwd_reg_kernel": "fwd_fused", "fwd_onehot_kernel": "fwd_fused",
               "dw_reduce_kernel": "bwd_dw_reduce",
               "sample_kernel<true>": "sample", "sample_kernel<false>": "sample_count",
+              "sample_kernel<true, 256>": "sample", "sample_kernel<true, 512>": "sample",
+              "sample_kernel<false, 256>": "sample_count", "sample_kernel<false, 512>": "sample_count",
               "lif_cell_kernel": "lif_cells", "lif_emit_kernel": "lif_emit",
               "stream_gather_kernel": "stream_gather", "stream_update_kernel": "stream_update"}
 

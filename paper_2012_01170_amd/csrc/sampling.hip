@@ -17,20 +17,49 @@
 //     point (all of them, or its ball neighbours).
 // Squared distances are float32 in the canonical form of the neighbour search,
 // so every choice is exact.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace sbc {
 namespace {
 
-constexpr int kSampThreads = 512;
 constexpr int kSampMax = 8192;  // points per cloud held in LDS
+// Clouds of up to kSampNear points keep their coordinates and row bounds in
+// LDS too, and their neighbours while the cloud has at most kSampEdges edges:
+// a farthest-point step is a chain (argmax, the chosen point's row, its
+// neighbours, their coordinates, the distances), and each link from memory
+// costs several times what it costs from LDS.
+constexpr int kSampNear = 2048;
+constexpr int kSampEdges = 24576;
 
 // the canonical form, with no contraction of the products into the sums
-__device__ __forceinline__ float sq_dist(const float *__restrict__ x, int64_t a, int64_t b) {
+__device__ __forceinline__ float sq_dist(const float3 &a, const float3 &b) {
 #pragma clang fp contract(off)
-    const float dx = x[3 * a] - x[3 * b], dy = x[3 * a + 1] - x[3 * b + 1],
-                dz = x[3 * a + 2] - x[3 * b + 2];
+    const float dx = a.x - b.x, dy = a.y - b.y, dz = a.z - b.z;
     return (dx * dx + dy * dy) + dz * dz;
+}
+
+// Maximum (minimum) over the wave by DPP operands (the value ends in lane 63,
+// returned to all): through LDS, as shuffles, each of the six steps is a round
+// trip.  Lanes a move leaves out take the identity, so each step is one
+// instruction.
+template <bool kMax>
+__device__ __forceinline__ int32_t wave_extreme(int32_t x) {
+    constexpr int32_t id = kMax ? INT32_MIN : INT32_MAX;
+#define SBC_DPP(ctrl, rows)                                                             \
+    do {                                                                                \
+        const int32_t y = __builtin_amdgcn_update_dpp(id, x, ctrl, rows, 0xf, false);   \
+        x = kMax ? (y > x ? y : x) : (y < x ? y : x);                                   \
+    } while (0)
+    SBC_DPP(0x111, 0xf);  // row_shr 1, 2, 4, 8: within 16 lanes
+    SBC_DPP(0x112, 0xf);
+    SBC_DPP(0x114, 0xf);
+    SBC_DPP(0x118, 0xf);
+    SBC_DPP(0x142, 0xa);  // row_bcast 15 and 31: across the rows of 16
+    SBC_DPP(0x143, 0xc);
+#undef SBC_DPP
+    return __builtin_amdgcn_readlane(x, 63);
 }
 
 struct SampleArgs {
@@ -46,14 +75,20 @@ struct SampleArgs {
 // kWrite false: the counting pass (each cloud's number of outputs; rejection
 // sampling alone decides its points here to count them); kWrite true: the
 // sampling, writing the indices at out_splits[b] and the squared distances.
-template <bool kWrite>
-__global__ void __launch_bounds__(kSampThreads) sample_kernel(SampleArgs A) {
+// T threads: a step scans n / T distances a thread and meets T / 64 waves.
+template <bool kWrite, int T>
+__global__ void __launch_bounds__(T) sample_kernel(SampleArgs A) {
     __shared__ float s_d[kSampMax];
+    __shared__ __attribute__((aligned(16))) int32_t s_word[kSampMax];
     __shared__ uint8_t s_st[kSampMax];  // 0 undecided, 1 taken, 2 rejected
-    __shared__ float s_bv[kSampThreads];
-    __shared__ int32_t s_bi[kSampThreads];
+    __shared__ float3 s_x[kSampNear];
+    __shared__ int32_t s_ptr[kSampNear + 1];
+    __shared__ uint16_t s_col[kSampEdges];
+    __shared__ __attribute__((aligned(16))) int64_t s_best[2][T / 64];
+    __shared__ int32_t s_count[T / 64];
     __shared__ int32_t s_cnt;
-    const int tid = threadIdx.x;
+    constexpr int kWaves = T / 64;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int32_t b = blockIdx.x;
     const int32_t s = A.splits[b], n = A.splits[b + 1] - s;
     const bool rej = A.method == SBC_SAMPLE_REJECTION || A.method == SBC_SAMPLE_APPROX_IFP_REJECTION;
@@ -66,7 +101,55 @@ __global__ void __launch_bounds__(kSampThreads) sample_kernel(SampleArgs A) {
         if (tid == 0) A.counts[b] = A.per_cloud < n ? A.per_cloud : n;
         return;
     }
-    for (int32_t j = tid; j < n; j += kSampThreads) {
+    const bool near = n <= kSampNear;
+    int32_t e_first = 0;
+    bool cols = false;  // the cloud's neighbours are in s_col
+    if (near) {
+        if (approx && n > 0) {
+            e_first = A.row_ptr[s];
+            const int32_t e_end = A.row_ptr[s + n];
+            cols = e_end >= e_first && e_end - e_first <= kSampEdges;
+            if (cols)
+                for (int32_t e = tid; e < e_end - e_first; e += T) {
+                    // (a neighbour outside the cloud is marked: it never counts)
+                    const int32_t k = A.col_idx[e_first + e] - s;
+                    s_col[e] = k >= 0 && k < n ? (uint16_t)k : (uint16_t)0xFFFF;
+                }
+        }
+        for (int32_t j = tid; j < n; j += T) {
+            const float *p = A.x + 3 * ((int64_t)s + j);
+            s_x[j] = make_float3(p[0], p[1], p[2]);
+            if (cols) s_ptr[j] = A.row_ptr[s + j] - e_first;
+        }
+        if (cols && tid == 0) s_ptr[n] = A.row_ptr[s + n] - e_first;
+    }
+    auto point = [&](int32_t j) {
+        if (near) return s_x[j];
+        const float *p = A.x + 3 * ((int64_t)s + j);
+        return make_float3(p[0], p[1], p[2]);
+    };
+    // row j's entries, and the neighbour of one (negative: outside the cloud).
+    // (Bounds that do not ascend belong to no ball pattern: in LDS they are kept
+    // inside the staged entries.)
+    auto row = [&](int32_t j, int32_t &e0, int32_t &e1) {
+        if (cols) {
+            const int32_t last = s_ptr[n];
+            e0 = s_ptr[j] > 0 ? s_ptr[j] : 0;
+            e1 = s_ptr[j + 1] < last ? s_ptr[j + 1] : last;
+        } else {
+            e0 = A.row_ptr[s + j];
+            e1 = A.row_ptr[s + j + 1];
+        }
+    };
+    auto neighbour = [&](int32_t e) {
+        if (cols) {
+            const uint16_t k = s_col[e];
+            return k == 0xFFFF ? -1 : (int32_t)k;
+        }
+        const int32_t k = A.col_idx[e] - s;
+        return k < n ? k : -1;
+    };
+    for (int32_t j = tid; j < n; j += T) {
         s_d[j] = INFINITY;
         s_st[j] = 0;
     }
@@ -77,12 +160,13 @@ __global__ void __launch_bounds__(kSampThreads) sample_kernel(SampleArgs A) {
         bool more = true;
         while (more) {
             bool undecided = false;
-            for (int32_t j = tid; j < n; j += kSampThreads) {
+            for (int32_t j = tid; j < n; j += T) {
                 if (s_st[j] != 0) continue;
                 bool pending = false, hit = false;
-                const int32_t e1 = A.row_ptr[s + j + 1];
-                for (int32_t e = A.row_ptr[s + j]; e < e1; ++e) {
-                    const int32_t k = A.col_idx[e] - s;
+                int32_t e, e1;
+                row(j, e, e1);
+                for (; e < e1; ++e) {
+                    const int32_t k = neighbour(e);
                     if (k < 0 || k >= j) continue;  // later points (and any outside the cloud)
                     const uint8_t st = s_st[k];
                     if (st == 1) { hit = true; break; }
@@ -96,13 +180,15 @@ __global__ void __launch_bounds__(kSampThreads) sample_kernel(SampleArgs A) {
         }
         // distances to the nearest taken neighbour; count the taken points
         int32_t mine = 0;
-        for (int32_t j = tid; j < n; j += kSampThreads) {
+        for (int32_t j = tid; j < n; j += T) {
             float d = INFINITY;
-            const int32_t e1 = A.row_ptr[s + j + 1];
-            for (int32_t e = A.row_ptr[s + j]; e < e1; ++e) {
-                const int32_t k = A.col_idx[e] - s;
-                if (k >= 0 && k < n && s_st[k] == 1) {
-                    const float q = sq_dist(A.x, (int64_t)s + k, (int64_t)s + j);
+            const float3 pj = point(j);
+            int32_t e, e1;
+            row(j, e, e1);
+            for (; e < e1; ++e) {
+                const int32_t k = neighbour(e);
+                if (k >= 0 && s_st[k] == 1) {
+                    const float q = sq_dist(point(k), pj);
                     d = q < d ? q : d;
                 }
             }
@@ -122,74 +208,186 @@ __global__ void __launch_bounds__(kSampThreads) sample_kernel(SampleArgs A) {
     const int32_t base = A.out_splits[b];
     int32_t pos = 0;
     if (rej) {
-        // the taken points first, in input order (a workgroup scan over chunks)
+        // the taken points first, in input order: each chunk of T points by wave
+        // ballots and the waves' counts
         const int32_t cap = taken < total ? taken : total;
-        for (int32_t c0 = 0; c0 < n; c0 += kSampThreads) {
+        for (int32_t c0 = 0; c0 < n; c0 += T) {
             const int32_t j = c0 + tid;
-            const int32_t f = (j < n && s_st[j] == 1) ? 1 : 0;
-            s_bi[tid] = f;
+            const bool f = j < n && s_st[j] == 1;
+            const uint64_t m = __ballot(f);
+            if (lane == 0) s_count[w] = (int32_t)__popcll(m);
             __syncthreads();
-            for (int d = 1; d < kSampThreads; d <<= 1) {
-                const int32_t y = tid >= d ? s_bi[tid - d] : 0;
-                __syncthreads();
-                s_bi[tid] += y;
-                __syncthreads();
+            int32_t rank = pos + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) {
+                const int32_t c = s_count[q];
+                if (q < w) rank += c;
+                pos += c;
             }
-            const int32_t rank = pos + s_bi[tid] - f;
             if (f && rank < cap) A.out_idx[base + rank] = s + j;
-            pos += s_bi[kSampThreads - 1];
             __syncthreads();
         }
         pos = cap;
     }
-    for (int32_t it = pos; it < total; ++it) {
-        // argmax of the distances over the points not yet taken, ties to the
-        // lowest index (a taken point is never taken again, which matters
-        // once every remaining distance is 0: coincident points)
-        float bv = -1.f;
-        int32_t bi = 0;
-        for (int32_t j = tid; j < n; j += kSampThreads) {
-            const float d = s_d[j];
-            if (s_st[j] != 1 && d > bv) { bv = d; bi = j; }
+    // Farthest points.  A point's word is its squared distance's bits, with the
+    // sign set once it is taken: as integers, candidates' words compare as their
+    // distances do and taken points' words lie below them all, so a taken point
+    // is never taken again (which matters once every remaining distance is 0:
+    // coincident points).  Ties go to the lowest index.
+    int32_t bk = -1, bi = 0;
+    const int32_t n4 = (n + 3) / 4;
+    for (int32_t j = tid; j < 4 * n4; j += T)
+        s_word[j] = j < n ? (int32_t)(__float_as_uint(s_d[j]) | (s_st[j] == 1 ? 0x80000000u : 0u))
+                          : INT32_MIN;
+    __syncthreads();
+    auto offer = [&](int32_t j, int32_t v) {
+        if (v > bk) {
+            bk = v;
+            bi = j;
         }
-        s_bv[tid] = bv;
-        s_bi[tid] = bi;
+    };
+    // the word of a point at distance q from the newly taken one
+    auto lowered = [](int32_t v, float q) {
+        return q < __uint_as_float((uint32_t)v & 0x7FFFFFFFu)
+                   ? (int32_t)(__float_as_uint(q) | ((uint32_t)v & 0x80000000u))
+                   : v;
+    };
+    // the workgroup's best candidate from the threads' (bk, bi)
+    auto argmax = [&](int32_t it) {
+        const int32_t wk = wave_extreme<true>(bk);
+        const uint64_t who = __ballot(bk == wk);
+        int32_t wi;
+        if (__popcll(who) == 1)  // the usual case
+            wi = __builtin_amdgcn_readlane(bi, (int)__builtin_ctzll(who));
+        else
+            wi = wave_extreme<false>(bk == wk ? bi : INT32_MAX);
+        // (the word, then the lowest index, in one comparison)
+        if (lane == 0)
+            s_best[it & 1][w] = (int64_t)(((uint64_t)(uint32_t)wk << 32) | (uint32_t)~wi);
         __syncthreads();
-        for (int d = kSampThreads / 2; d >= 1; d >>= 1) {
-            if (tid < d) {
-                const float v2 = s_bv[tid + d];
-                const int32_t i2 = s_bi[tid + d];
-                if (v2 > s_bv[tid] || (v2 == s_bv[tid] && i2 < s_bi[tid])) {
-                    s_bv[tid] = v2;
-                    s_bi[tid] = i2;
-                }
+        int64_t c[kWaves];
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) c[q] = s_best[it & 1][q];
+#pragma unroll
+        for (int q = 1; q < kWaves; ++q) c[0] = c[q] > c[0] ? c[q] : c[0];
+        return __builtin_amdgcn_readfirstlane((int32_t)~(uint32_t)c[0]);
+    };
+    // Thread (it - pos) % T keeps the point taken in step it; they are stored T
+    // steps at a time (a store in every step would be waited for).
+    int32_t mine = 0;
+    auto record = [&](int32_t it, int32_t sel) {
+        const int32_t slot = (it - pos) % T;
+        if (tid == slot) mine = s + sel;
+        if ((slot == T - 1 || it + 1 == total) && tid <= slot)
+            A.out_idx[base + it - slot + tid] = mine;
+    };
+    // Steps that lower the chosen point's ball.  Where points, rows and
+    // neighbours come from is chosen outside the loop: with the choice inside,
+    // every step waited for the memory path's loads and stores.
+    auto ball_steps = [&](auto coords, auto bounds, auto entry) {
+        for (int32_t it = pos; it < total; ++it) {
+            bk = -1;
+            bi = 0;
+#pragma unroll 2
+            for (int32_t j = tid; j < n4; j += T) {
+                const int4 k = *reinterpret_cast<const int4 *>(&s_word[4 * j]);
+                offer(4 * j, k.x);
+                offer(4 * j + 1, k.y);
+                offer(4 * j + 2, k.z);
+                offer(4 * j + 3, k.w);
             }
+            const int32_t sel = argmax(it);
+            const float3 ps = coords(sel);
+            int32_t e, e1;
+            bounds(sel, e, e1);
+            for (e += tid; e < e1; e += T) {
+                const int32_t k = entry(e);
+                if (k < 0) continue;
+                const int32_t v = lowered(s_word[k], sq_dist(coords(k), ps));
+                s_word[k] = k == sel ? v | INT32_MIN : v;
+            }
+            // (its ball holds the chosen point itself unless the pattern leaves it
+            // out; the two writes of its word agree in any order)
+            if (tid == 0) atomicOr(&s_word[sel], INT32_MIN);
+            record(it, sel);
             __syncthreads();
         }
-        const int32_t sel = s_bi[0];
-        if (tid == 0) {
-            A.out_idx[base + it] = s + sel;
-            s_st[sel] = 1;  // read again only after the barrier closing this step
+    };
+    // Steps that lower every point, kept in registers (n <= NP T points, thread
+    // tid the points tid, tid + T, ...): no word is shared, so a step has one
+    // barrier.
+    auto all_steps = [&](auto np) {
+        constexpr int NP = decltype(np)::value;
+        float3 x[NP];
+        int32_t v[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int32_t j = tid + q * T;
+            v[q] = j < n ? s_word[j] : INT32_MIN;
+            x[q] = j < n ? point(j) : make_float3(0.f, 0.f, 0.f);
         }
-        if (approx) {
-            const int32_t e0 = A.row_ptr[s + sel], e1 = A.row_ptr[s + sel + 1];
-            for (int32_t e = e0 + tid; e < e1; e += kSampThreads) {
-                const int32_t k = A.col_idx[e] - s;
-                if (k >= 0 && k < n) {
-                    const float q = sq_dist(A.x, (int64_t)s + k, (int64_t)s + sel);
-                    if (q < s_d[k]) s_d[k] = q;
-                }
+        auto offer_all = [&]() {
+            bk = -1;
+            bi = 0;
+#pragma unroll
+            for (int q = 0; q < NP; ++q) offer(tid + q * T, v[q]);
+        };
+        offer_all();
+        for (int32_t it = pos; it < total; ++it) {
+            const int32_t sel = argmax(it);
+            const float3 ps = point(sel);
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const int32_t j = tid + q * T;
+                if (j == sel) v[q] |= INT32_MIN;
+                if (j < n) v[q] = lowered(v[q], sq_dist(x[q], ps));
             }
-        } else {
-            for (int32_t j = tid; j < n; j += kSampThreads) {
-                const float q = sq_dist(A.x, (int64_t)s + j, (int64_t)s + sel);
-                if (q < s_d[j]) s_d[j] = q;
-            }
+            offer_all();
+            record(it, sel);
         }
-        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+            if (tid + q * T < n) s_word[tid + q * T] = v[q];
+    };
+    auto lds_point = [&](int32_t j) { return s_x[j]; };
+    auto mem_point = [&](int32_t j) {
+        const float *p = A.x + 3 * ((int64_t)s + j);
+        return make_float3(p[0], p[1], p[2]);
+    };
+    const int32_t e_last = cols ? s_ptr[n] : 0;
+    auto lds_row = [&](int32_t j, int32_t &e0, int32_t &e1) {
+        e0 = s_ptr[j] > 0 ? s_ptr[j] : 0;
+        e1 = s_ptr[j + 1] < e_last ? s_ptr[j + 1] : e_last;
+    };
+    auto mem_row = [&](int32_t j, int32_t &e0, int32_t &e1) {
+        e0 = A.row_ptr[s + j];
+        e1 = A.row_ptr[s + j + 1];
+    };
+    auto lds_entry = [&](int32_t e) {
+        const uint16_t k = s_col[e];
+        return k == 0xFFFF ? -1 : (int32_t)k;
+    };
+    auto mem_entry = [&](int32_t e) {
+        const int32_t k = A.col_idx[e] - s;
+        return k < n ? k : -1;
+    };
+    if (!approx) {
+        if (n <= 4 * T) all_steps(std::integral_constant<int, 4>{});
+        else if (n <= 8 * T) all_steps(std::integral_constant<int, 8>{});
+        else if (n <= 16 * T) all_steps(std::integral_constant<int, 16>{});
+        else all_steps(std::integral_constant<int, kSampMax / T>{});
+    } else if (cols) {
+        ball_steps(lds_point, lds_row, lds_entry);
+    } else if (near) {
+        ball_steps(lds_point, mem_row, mem_entry);
+    } else {
+        ball_steps(mem_point, mem_row, mem_entry);
     }
-    if (A.dmin2)
-        for (int32_t j = tid; j < n; j += kSampThreads) A.dmin2[s + j] = s_d[j];
+    if (A.dmin2) {
+        __syncthreads();
+        for (int32_t j = tid; j < n; j += T)
+            A.dmin2[s + j] = __uint_as_float((uint32_t)s_word[j] & 0x7FFFFFFFu);
+    }
 }
 
 }  // namespace
@@ -242,15 +440,25 @@ extern "C" sbc_status sbc_sample_points(const float *x, const int32_t *splits, i
     A.dmin2 = nullptr;
     // counts per cloud (rejection sampling runs once here to count), bounds,
     // then the sampling with its writes
+    // 256 threads where no cloud has more than kSampNear points (a step's scan is
+    // then at most 8 distances a thread), else 512
+    const bool small = max_cloud <= kSampNear;
+    auto launch = [&](auto write) {
+        constexpr bool kW = decltype(write)::value;
+        if (small)
+            hipLaunchKernelGGL((sample_kernel<kW, 256>), dim3(n_batch), dim3(256), 0, stream, A);
+        else
+            hipLaunchKernelGGL((sample_kernel<kW, 512>), dim3(n_batch), dim3(512), 0, stream, A);
+    };
     trace_before("sample_count", stream);
-    hipLaunchKernelGGL(sample_kernel<false>, dim3(n_batch), dim3(kSampThreads), 0, stream, A);
+    launch(std::false_type{});
     SBC_LAUNCH_CHECK();
     trace_after("sample_count", stream);
     SBC_TRY(exclusive_scan_i32(counts, out_splits, n_batch, total, scan_ws, stream));
     A.out_splits = out_splits;
     A.dmin2 = dmin2;
     trace_before("sample", stream);
-    hipLaunchKernelGGL(sample_kernel<true>, dim3(n_batch), dim3(kSampThreads), 0, stream, A);
+    launch(std::true_type{});
     SBC_LAUNCH_CHECK();
     trace_after("sample", stream);
     return SBC_OK;
