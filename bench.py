@@ -80,6 +80,7 @@ TRACE_NAME = {"bwd_ws_kernel": "bwd_fused",
               "dw_reduce_kernel": "bwd_dw_reduce",
               "sample_kernel<true>": "sample", "sample_kernel<false>": "sample_count",
               "sample_kernel<true, 256>": "sample", "sample_kernel<true, 512>": "sample",
+              "featureless_reduce_kernel": "featureless_dphi",
               "sample_kernel<false, 256>": "sample_count", "sample_kernel<false, 512>": "sample_count",
               "lif_cell_kernel": "lif_cells", "lif_emit_kernel": "lif_emit",
               "stream_gather_kernel": "stream_gather", "stream_update_kernel": "stream_update"}
@@ -94,7 +95,8 @@ def trace_name(kernel):
         args = kernel[len(base) + 1:].split(",")
         return "decay_fused" if len(args) > 3 and args[3].strip() == "16" else "bwd_fused"
     if base == "featureless_kernel":  # <M, mode, writes Z>
-        return "featureless_fwd" if kernel.rstrip(">").endswith("true") else "featureless_rowsum"
+        # (the row sums of the backward sit in a kernel of their own now)
+        return "featureless_rowsum" if kernel.rstrip(">").endswith("false") else "featureless_fwd"
     if base == "spmm_kernel":  # <M, contract, X type>: named by direction, see SPMM_DIRECTION
         args = kernel[len(base) + 1:].split(",")
         return "spmm_contract" if len(args) > 1 and args[1].strip() == "true" else "spmm_expand"

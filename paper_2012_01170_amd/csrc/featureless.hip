@@ -5,14 +5,15 @@
 //
 // Forward: a group of kFLanes lanes per row takes the row's edges in turn,
 // evaluates their basis values (or reads them), and adds them up in float64,
-// lane partial sums first and then a butterfly, so the sums do not depend on
-// scheduling; the group then writes Z[i, :] = G~[i, :] Phi_0, a lane per
-// output channel.  Backward: dPhi_0 = G~^T dZ; the same kernel writes G~ into
-// the workspace and the dense contraction (split over rows, summed in split
-// order) multiplies it by dZ.
+// lane partial sums first and then across the lanes, so the sums do not depend
+// on scheduling; the group then writes Z[i, :] = G~[i, :] Phi_0, a lane per
+// output channel.  Backward: dPhi_0 = G~^T dZ; a block makes G~ of kDRows rows
+// at a time in LDS and keeps its part of the product in registers, and the
+// blocks' parts are added in order (G~ never reaches memory).
+#include <type_traits>
+
 #include "basis.hpp"
 #include "common.hpp"
-#include "gemm.hpp"
 #include "spmm.hpp"
 
 namespace sbc {
@@ -21,17 +22,35 @@ namespace {
 constexpr int kFLanes = 16;
 constexpr int kFThreads = 256;
 
+// Sum over the 16 lanes of a DPP row, in every lane: xor 1, xor 2, then the
+// mirrored quads and halves.  (Moves within the vector ALU; as shuffles through
+// LDS the 4 steps of M float64 sums took longer than the edges.)
+__device__ __forceinline__ double row16_sum(double x) {
+#define SBC_STEP(ctrl)                                                              \
+    do {                                                                            \
+        const int64_t u = __builtin_bit_cast(int64_t, x);                           \
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)u, ctrl, 0xf, 0xf, true); \
+        const uint32_t hi =                                                         \
+            (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), ctrl, 0xf, 0xf, true); \
+        x += __builtin_bit_cast(double, (int64_t)(((uint64_t)hi << 32) | lo));      \
+    } while (0)
+    SBC_STEP(0xB1);   // quad_perm [1, 0, 3, 2]
+    SBC_STEP(0x4E);   // quad_perm [2, 3, 0, 1]
+    SBC_STEP(0x141);  // row_half_mirror
+    SBC_STEP(0x140);  // row_mirror
+#undef SBC_STEP
+    return x;
+}
+
+// G~[r, :] in every lane of the row's group (sl: the lane in it).
 // kMode: 0 basis values read from v; 1 windowed point monomials; 2 event
-// offsets with decay; 3 the weighted monomials (Eq. 11).
-template <int M, int kMode, bool kWriteZ>
-__global__ void __launch_bounds__(kFThreads)
-    featureless_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
-                       const int32_t *__restrict__ col_idx, int64_t nnz_bound,
-                       const float *__restrict__ v, sbc_geometry g,
-                       const float *__restrict__ Phi, int32_t P, float *__restrict__ out) {
-    const int sl = threadIdx.x % kFLanes;
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kFLanes;
-    if (r >= n_rows) return;  // a group leaves as a whole
+// offsets with decay; 3 the weighted monomials (Eq. 11), whose common factor
+// 1 / W_i is taken out of the row's sums.
+template <int M, int kMode>
+__device__ __forceinline__ void row_sums(int64_t r, int sl, const int32_t *__restrict__ row_ptr,
+                                         const int32_t *__restrict__ col_idx, int64_t nnz_bound,
+                                         const float *__restrict__ v, const sbc_geometry &g,
+                                         double (&acc)[M]) {
     // entries past nnz_bound (a malformed pattern) are not read
     const int64_t e1 = row_ptr[r + 1] < nnz_bound ? (int64_t)row_ptr[r + 1] : nnz_bound;
     const int64_t e0 = row_ptr[r] < e1 ? (int64_t)row_ptr[r] : e1;
@@ -43,91 +62,194 @@ __global__ void __launch_bounds__(kFThreads)
         qy = g.x_out[3 * r + 1];
         qz = g.x_out[3 * r + 2];
     }
-    // the weighted basis normalises by the row's weight sum
-    double wsum = 0.0;
-    if constexpr (kMode == 3) {
-        for (int64_t e = e0 + sl; e < e1; e += kFLanes) {
-            const int64_t j = col_idx[e];
-            wsum += point_weight(qx, qy, qz, g.x_in[3 * j], g.x_in[3 * j + 1], g.x_in[3 * j + 2],
-                                 inv_r);
-        }
-#pragma unroll
-        for (int d = kFLanes / 2; d >= 1; d >>= 1) wsum += __shfl_xor(wsum, d, kFLanes);
-    }
-    double acc[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) acc[m] = 0.0;
     for (int64_t e = e0 + sl; e < e1; e += kFLanes) {
-        float b[M];
-        if constexpr (kMode == 0) {
-#pragma unroll
-            for (int m = 0; m < M; ++m) b[m] = v[e * M + m];
-        } else if constexpr (kMode == 1) {
-            const int64_t j = col_idx[e];
-            point_basis<M>(qx, qy, qz, g.x_in[3 * j], g.x_in[3 * j + 1], g.x_in[3 * j + 2], inv_r,
-                           b);
-        } else if constexpr (kMode == 2) {
-            const int64_t j = col_idx[e];
-            const int k = event_index(g.px[r] - g.px[j], g.py[r] - g.py[j]);
-            const float d = event_decay(g.t[r], g.t[j], inv_tau);
-#pragma unroll
-            for (int m = 0; m < M; ++m) b[m] = m == k ? d : 0.f;
-        } else {
+        if constexpr (kMode == 3) {
             const int64_t j = col_idx[e];
             const float px = g.x_in[3 * j], py = g.x_in[3 * j + 1], pz = g.x_in[3 * j + 2];
             const double w = point_weight(qx, qy, qz, px, py, pz, inv_r);
-            weighted_mono10(qx, qy, qz, px, py, pz, inv_r, wsum != 0.0 ? w / wsum : 0.0, b);
-        }
+            const double x = ((double)qx - (double)px) * inv_r;
+            const double y = ((double)qy - (double)py) * inv_r;
+            const double z = ((double)qz - (double)pz) * inv_r;
+            const double wx = w * x, wy = w * y, wz = w * z;
+            acc[0] += w;
+            acc[1] += wx;
+            acc[2] += wy;
+            acc[3] += wz;
+            acc[4] += wx * x;
+            acc[5] += wy * y;
+            acc[6] += wz * z;
+            acc[7] += wx * y;
+            acc[8] += wx * z;
+            acc[9] += wy * z;
+        } else {
+            float b[M];
+            if constexpr (kMode == 0) {
 #pragma unroll
-        for (int m = 0; m < M; ++m) acc[m] += (double)b[m];
+                for (int m = 0; m < M; ++m) b[m] = v[e * M + m];
+            } else if constexpr (kMode == 1) {
+                const int64_t j = col_idx[e];
+                point_basis<M>(qx, qy, qz, g.x_in[3 * j], g.x_in[3 * j + 1], g.x_in[3 * j + 2],
+                               inv_r, b);
+            } else {
+                const int64_t j = col_idx[e];
+                const int k = event_index(g.px[r] - g.px[j], g.py[r] - g.py[j]);
+                const float d = event_decay(g.t[r], g.t[j], inv_tau);
+#pragma unroll
+                for (int m = 0; m < M; ++m) b[m] = m == k ? d : 0.f;
+            }
+#pragma unroll
+            for (int m = 0; m < M; ++m) acc[m] += (double)b[m];
+        }
     }
 #pragma unroll
-    for (int d = kFLanes / 2; d >= 1; d >>= 1)
+    for (int m = 0; m < M; ++m) acc[m] = row16_sum(acc[m]);
+    if constexpr (kMode == 3) {
+        const double s = acc[0] != 0.0 ? 1.0 / acc[0] : 0.0;
 #pragma unroll
-        for (int m = 0; m < M; ++m) acc[m] += __shfl_xor(acc[m], d, kFLanes);
-    if constexpr (!kWriteZ) {
-        if (sl < M) {
-            float gm = 0.f;
-#pragma unroll
-            for (int m = 0; m < M; ++m)
-                if (m == sl) gm = (float)acc[m];
-            out[r * M + sl] = gm;
-        }
-    } else {
-        for (int32_t p = sl; p < P; p += kFLanes) {
-            double z = 0.0;
-#pragma unroll
-            for (int m = 0; m < M; ++m) z += acc[m] * (double)Phi[(int64_t)m * P + p];
-            out[r * P + p] = (float)z;
-        }
+        for (int m = 0; m < M; ++m) acc[m] *= s;
     }
 }
 
-template <bool kWriteZ>
-sbc_status launch_featureless(const sbc_csr *csr, const float *v, const sbc_geometry *g,
-                              int32_t M, const float *Phi, int32_t P, float *out,
-                              hipStream_t stream) {
-    const dim3 grid(grid_for((int64_t)csr->n_rows * kFLanes, kFThreads)), block(kFThreads);
-    const int mode = v ? 0
-                       : g->basis == SBC_BASIS_EVENT8 ? 2
-                       : g->basis == SBC_BASIS_WMONO10 ? 3 : 1;
-    const sbc_geometry gg = g ? *g : sbc_geometry{};
-#define SBC_FL(MM, MODE)                                                                        \
-    hipLaunchKernelGGL((featureless_kernel<MM, MODE, kWriteZ>), grid, block, 0, stream,          \
-                       csr->n_rows, csr->row_ptr, csr->col_idx, csr->nnz_bound, v, gg, Phi, P, \
-                       out)
-    if (mode == 0) {
-        if (M == 4) SBC_FL(4, 0); else if (M == 8) SBC_FL(8, 0); else SBC_FL(10, 0);
-    } else if (mode == 1) {
-        if (M == 4) SBC_FL(4, 1); else SBC_FL(8, 1);
-    } else if (mode == 2) {
+template <int M, int kMode>
+__global__ void __launch_bounds__(kFThreads)
+    featureless_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
+                       const int32_t *__restrict__ col_idx, int64_t nnz_bound,
+                       const float *__restrict__ v, sbc_geometry g,
+                       const float *__restrict__ Phi, int32_t P, float *__restrict__ out) {
+    const int sl = threadIdx.x % kFLanes;
+    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kFLanes;
+    if (r >= n_rows) return;  // a group leaves as a whole
+    double acc[M];
+    row_sums<M, kMode>(r, sl, row_ptr, col_idx, nnz_bound, v, g, acc);
+    for (int32_t p = sl; p < P; p += kFLanes) {
+        double z = 0.0;
+#pragma unroll
+        for (int m = 0; m < M; ++m) z += acc[m] * (double)Phi[(int64_t)m * P + p];
+        out[r * P + p] = (float)z;
+    }
+}
+
+// Rows of G~ a block makes at a time, and the columns of dZ its threads take at
+// a time (blockIdx.y: which kDCols).
+constexpr int kDRows = 64;
+constexpr int kDCols = 64;
+constexpr int kDBlocks = 512;  // partial products: two blocks per CU
+
+// part[x][m, p] = sum over the block's rows r of G~[r, m] dZ[r, p].  Thread
+// (column p of kDCols, row group q of 4) sums the rows r = q mod 4 in float64;
+// the groups are added in order.  Where there are at most 32 columns a row of
+// threads is 32 wide and there are 8 groups.
+template <int M, int kMode>
+__global__ void __launch_bounds__(kFThreads)
+    featureless_dphi_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
+                            const int32_t *__restrict__ col_idx, int64_t nnz_bound,
+                            const float *__restrict__ v, sbc_geometry g,
+                            const float *__restrict__ dZ, int32_t P, float *__restrict__ part) {
+    __shared__ float G[kDRows][M];
+    __shared__ double sums[kFThreads];
+    const int tid = threadIdx.x, sl = tid % kFLanes;
+    const int32_t p0 = blockIdx.y * kDCols;
+    const int width = P - p0 <= 32 ? 32 : 64;
+    const int32_t p = p0 + tid % width;
+    const int q = tid / width, groups = kFThreads / width;
+    double acc[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) acc[m] = 0.0;
+    for (int64_t r0 = (int64_t)blockIdx.x * kDRows; r0 < n_rows; r0 += (int64_t)gridDim.x * kDRows) {
+#pragma unroll 1
+        for (int i = tid / kFLanes; i < kDRows; i += kFThreads / kFLanes) {
+            double s[M];
+            const bool on = r0 + i < n_rows;  // the same for a whole group
+            if (on) row_sums<M, kMode>(r0 + i, sl, row_ptr, col_idx, nnz_bound, v, g, s);
+            if (sl < M) {
+                float x = 0.f;
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+                    if (m == sl) x = on ? (float)s[m] : 0.f;
+                G[i][sl] = x;
+            }
+        }
+        __syncthreads();
+        if (p < P) {
+            const int64_t left = n_rows - r0;
+            const int rows = left < kDRows ? (int)left : kDRows;
+            for (int i = q; i < rows; i += groups) {
+                const double z = (double)dZ[(r0 + i) * P + p];
+#pragma unroll
+                for (int m = 0; m < M; ++m) acc[m] += (double)G[i][m] * z;
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        sums[tid] = acc[m];
+        __syncthreads();
+        if (q == 0 && p < P) {
+            double t = 0.0;
+            for (int k = 0; k < groups; ++k) t += sums[k * width + tid];
+            part[((int64_t)blockIdx.x * M + m) * P + p] = (float)t;
+        }
+        __syncthreads();
+    }
+}
+
+// dPhi[x] = sum over blocks of part[block][x], in block order within 16 groups
+// of consecutive blocks (a thread per position and group), then over the groups.
+__global__ void __launch_bounds__(256)
+    featureless_reduce_kernel(const float *__restrict__ part, int32_t n_parts, int32_t total,
+                              float *__restrict__ dPhi) {
+    __shared__ double s[16][16];
+    const int g = threadIdx.x / 16, t = threadIdx.x % 16;
+    const int32_t x = blockIdx.x * 16 + t;
+    const int32_t per = (n_parts + 15) / 16;
+    const int32_t b0 = g * per, b1 = b0 + per < n_parts ? b0 + per : n_parts;
+    double a = 0.0;
+    if (x < total)
+        for (int32_t b = b0; b < b1; b += 8) {
+            float y[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[j] = b + j < b1 ? part[(int64_t)(b + j) * total + x] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a += (double)y[j];
+        }
+    s[g][t] = a;
+    __syncthreads();
+    if (g == 0 && x < total) {
+        double r = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) r += s[k][t];
+        dPhi[x] = (float)r;
+    }
+}
+
+int32_t dphi_blocks(int32_t n) {
+    const int32_t b = (n + kDRows - 1) / kDRows;
+    return b < kDBlocks ? b : kDBlocks;
+}
+
+// f(M, mode) for the basis of a call
+template <typename F>
+void featureless_dispatch(const float *v, const sbc_geometry *g, int32_t M, F f) {
+    using std::integral_constant;
+    auto at = [&](auto m, auto mode) { f(m, mode); };
+#define SBC_FL(MM, MODE) at(integral_constant<int, MM>{}, integral_constant<int, MODE>{})
+    if (v) {
+        if (M == 4) SBC_FL(4, 0);
+        else if (M == 8) SBC_FL(8, 0);
+        else SBC_FL(10, 0);
+    } else if (g->basis == SBC_BASIS_EVENT8) {
         SBC_FL(8, 2);
-    } else {
+    } else if (g->basis == SBC_BASIS_WMONO10) {
         SBC_FL(10, 3);
+    } else if (M == 4) {
+        SBC_FL(4, 1);
+    } else {
+        SBC_FL(8, 1);
     }
 #undef SBC_FL
-    SBC_LAUNCH_CHECK();
-    return SBC_OK;
 }
 
 sbc_status check_featureless(const sbc_csr *csr, const float *v, const sbc_geometry *g,
@@ -152,7 +274,7 @@ using namespace sbc;
 
 extern "C" size_t sbc_featureless_workspace_size(int32_t n_out, int32_t M, int32_t P) {
     if (n_out < 0 || M <= 0 || P <= 0) return 0;
-    return align_up((size_t)n_out * M * 4) + gemm_workspace_floats(M, P, n_out) * 4;
+    return align_up((size_t)dphi_blocks(n_out) * M * P * 4);
 }
 
 extern "C" sbc_status sbc_featureless_forward(const sbc_csr *csr, const float *v,
@@ -164,7 +286,14 @@ extern "C" sbc_status sbc_featureless_forward(const sbc_csr *csr, const float *v
     if (csr->n_rows == 0) return SBC_OK;
     if (!Phi || !Z) return fail(SBC_ERR_INVALID_ARG, "Phi or Z is null");
     trace_before("featureless_fwd", stream);
-    SBC_TRY(launch_featureless<true>(csr, v, geometry, M, Phi, P, Z, stream));
+    const sbc_geometry g = geometry ? *geometry : sbc_geometry{};
+    featureless_dispatch(v, geometry, M, [&](auto m, auto mode) {
+        hipLaunchKernelGGL((featureless_kernel<decltype(m)::value, decltype(mode)::value>),
+                           dim3(grid_for((int64_t)csr->n_rows * kFLanes, kFThreads)),
+                           dim3(kFThreads), 0, stream, csr->n_rows, csr->row_ptr, csr->col_idx,
+                           csr->nnz_bound, v, g, Phi, P, Z);
+    });
+    SBC_LAUNCH_CHECK();
     trace_after("featureless_fwd", stream);
     return SBC_OK;
 }
@@ -183,13 +312,22 @@ extern "C" sbc_status sbc_featureless_backward(const sbc_csr *csr, const float *
     if (!workspace || workspace_bytes < need)
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_featureless_workspace_size()");
     if (n == 0) return fill_i32(reinterpret_cast<int32_t *>(dPhi), 0, (int64_t)M * P, stream);
-    float *Gt = static_cast<float *>(workspace);
-    float *part = reinterpret_cast<float *>(static_cast<char *>(workspace) +
-                                            align_up((size_t)n * M * 4));
+    float *part = static_cast<float *>(workspace);
+    const sbc_geometry g = geometry ? *geometry : sbc_geometry{};
+    const int32_t blocks = dphi_blocks(n);
     trace_before("featureless_rowsum", stream);
-    SBC_TRY(launch_featureless<false>(csr, v, geometry, M, nullptr, P, Gt, stream));
+    featureless_dispatch(v, geometry, M, [&](auto m, auto mode) {
+        hipLaunchKernelGGL((featureless_dphi_kernel<decltype(m)::value, decltype(mode)::value>),
+                           dim3((unsigned)blocks, (unsigned)((P + kDCols - 1) / kDCols)),
+                           dim3(kFThreads), 0, stream, n, csr->row_ptr, csr->col_idx,
+                           csr->nnz_bound, v, g, dZ, P, part);
+    });
+    SBC_LAUNCH_CHECK();
     trace_after("featureless_rowsum", stream);
-    // dPhi [M, P] = G~^T [M, n] x dZ [n, P]
-    return gemm(Gt, false, 1, M, dZ, false, P, 1, dPhi, P, 1, M, P, n, part, stream,
-                "featureless_dphi");
+    trace_before("featureless_dphi", stream);
+    hipLaunchKernelGGL(featureless_reduce_kernel, dim3(grid_for((int64_t)M * P, 16)), dim3(256), 0,
+                       stream, part, blocks, M * P, dPhi);
+    SBC_LAUNCH_CHECK();
+    trace_after("featureless_dphi", stream);
+    return SBC_OK;
 }

@@ -1,5 +1,6 @@
 """The sampler at the sizes where its storage changes (points per thread, the
-clouds whose coordinates, rows and neighbours stay on the CU)."""
+clouds whose coordinates, rows and neighbours stay on the CU) and the
+featureless backward at the edges of its row and column blocks."""
 import numpy as np
 import pytest
 import torch
@@ -60,3 +61,21 @@ def test_sampling_pattern_without_self_edges():
     ref, dref = oracle.sampling.approx_ifp(x, splits, [50], rp2, ci2)
     assert sorted(idx.cpu().numpy().tolist()) == list(range(50))
     assert np.array_equal(idx.cpu().numpy(), ref) and np.array_equal(d2.cpu().numpy(), dref)
+
+
+@pytest.mark.parametrize("n,P", [(1, 1), (63, 32), (65, 33), (700, 64), (700, 129)])
+@pytest.mark.parametrize("basis", [workloads.BASIS_MONO4, workloads.BASIS_MONO8,
+                                   workloads.BASIS_WMONO10])
+def test_featureless_block_edges(n, P, basis):
+    w = workloads.small_points(seed=72, n_clouds=1, n=n, c_in=1, c_out=P, basis=basis)
+    rp, ci = oracle.points_csr(w["x_in"], w["in_splits"], w["x_out"], w["out_splits"], w["radius"],
+                               w["k_cap"])
+    v = oracle.basis.point_values(basis, w["x_in"], w["x_out"], rp, ci, w["radius"], w["M"])
+    t = G.to_device(w)
+    csr = G.search(w, t)
+    geo = G.geometry(w, t)
+    Phi = np.ascontiguousarray(w["W"][:, 0, :])
+    Z = G.sbc.featureless_forward(csr, G.dev(Phi), geometry=geo).cpu().numpy()
+    dPhi = G.sbc.featureless_backward(csr, t["dY"], w["M"], geometry=geo).cpu().numpy()
+    assert G.norm_error(Z, oracle.conv.featureless_forward(rp, ci, v, Phi)[0]) < G.TOL_F32
+    assert G.norm_error(dPhi, oracle.conv.featureless_backward(rp, ci, v, w["dY"])) < G.TOL_F32
