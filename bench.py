@@ -83,6 +83,8 @@ TRACE_NAME = {"bwd_ws_kernel": "bwd_fused",
               "featureless_reduce_kernel": "featureless_dphi",
               "sample_kernel<false, 256>": "sample_count", "sample_kernel<false, 512>": "sample_count",
               "lif_cell_kernel": "lif_cells", "lif_emit_kernel": "lif_emit",
+              "stream_link_kernel": "stream_lists", "stream_output_kernel": "stream_gather",
+              "stream_state_kernel": "stream_update",
               "stream_gather_kernel": "stream_gather", "stream_update_kernel": "stream_update"}
 
 
@@ -94,8 +96,7 @@ def trace_name(kernel):
     if base == "bwd_ws_kernel":  # <M, CI, CO, basis, ...>: basis 16 is the decay derivative
         args = kernel[len(base) + 1:].split(",")
         return "decay_fused" if len(args) > 3 and args[3].strip() == "16" else "bwd_fused"
-    if base == "featureless_kernel":  # <M, mode, writes Z>
-        # (the row sums of the backward sit in a kernel of their own now)
+    if base == "featureless_kernel":  # <M, mode>; profiles kept from before: <M, mode, writes Z>
         return "featureless_rowsum" if kernel.rstrip(">").endswith("false") else "featureless_fwd"
     if base == "spmm_kernel":  # <M, contract, X type>: named by direction, see SPMM_DIRECTION
         args = kernel[len(base) + 1:].split(",")
@@ -374,6 +375,14 @@ def lif_table(n, npix, slots, spikes):
 def stream_table(B, npix, C, P):
     """Kernels of one batch of the deployment form (each runs once per batch):
     name -> (launches per batch, algorithmic bytes, flops, MFMA)."""
+    if B <= 8192:  # linked events: lists, outputs (G and its product), state
+        links = 8 * B + 4 * B
+        return {
+            "stream_lists": (1, 12 * B + links + 4 * B, 0, False),
+            "stream_gather": (1, 12 * B + links + 4 * npix + 4 * npix * C + 4 * B * C
+                              + 4 * 8 * C * P + 4 * B * P, 2 * B * 8 * C * P, True),
+            "stream_update": (1, links + 4 * B * C + 8 * B * C + 8 * B, 0, False),
+        }
     lists = 12 * B + 8 * B + 4 * (npix + 1)
     return {
         "stream_lists": (1, lists, 0, False),
