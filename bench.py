@@ -83,6 +83,7 @@ TRACE_NAME = {"bwd_ws_kernel": "bwd_fused",
               "featureless_reduce_kernel": "featureless_dphi",
               "sample_kernel<false, 256>": "sample_count", "sample_kernel<false, 512>": "sample_count",
               "lif_cell_kernel": "lif_cells", "lif_emit_kernel": "lif_emit",
+              "lif_count_kernel": "lif_emit",
               "stream_link_kernel": "stream_lists", "stream_output_kernel": "stream_gather",
               "stream_state_kernel": "stream_update",
               "stream_gather_kernel": "stream_gather", "stream_update_kernel": "stream_update"}
@@ -364,11 +365,12 @@ def sampling_table(n, E, n_batch):
 def lif_table(n, npix, slots, spikes):
     """Kernels of one LIF step (pixel lists, the cells, the emission): name ->
     (launches, algorithmic bytes, flops, MFMA).  lif_sort spans the key,
-    sort, bounds and time kernels and the flag clear."""
+    sort, bounds and time kernels and the flag clear, lif_emit the count too."""
+    words = 4 * n * ((slots + 3) // 4)  # a byte per slot, whole words an event
     return {
-        "lif_sort": (1, 12 * n + 8 * n + 4 * (npix + 1) + 4 * n * slots, 0, False),
-        "lif_cells": (1, 4 * (npix + 1) + 8 * n + 4 * spikes, 0, False),
-        "lif_emit": (1, 8 * n * slots + 12 * spikes + 16 * spikes, 0, False),
+        "lif_sort": (1, 12 * n + 8 * n + 4 * (npix + 1) + words, 0, False),
+        "lif_cells": (1, 4 * (npix + 1) + 8 * n + spikes, 0, False),
+        "lif_emit": (1, 2 * words + 12 * spikes + 16 * spikes, 0, False),
     }
 
 
