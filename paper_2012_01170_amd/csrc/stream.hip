@@ -412,18 +412,17 @@ StreamWs carve_stream(void *base, int32_t n, int64_t npix, int32_t M, int32_t C_
                       int32_t C_out, size_t *bytes) {
     Carver cv(base);
     StreamWs w{};
-    if (short_batch(n, M * C_in)) {
-        w.link = cv.take<int2>(n);
-        w.tail_key = cv.take<int32_t>(n);
-        w.tail = cv.take<int32_t>(npix);
-        if (bytes) *bytes = cv.used;
-        return w;
-    }
     w.pl = carve_pixel_lists(cv, n, npix);
     w.status = cv.take<uint32_t>(4);
     w.G = cv.take<float>((size_t)n * M * C_in);
     w.part = cv.take<float>(gemm_workspace_floats(n, C_out, (int64_t)M * C_in));
-    if (bytes) *bytes = cv.used;
+    // a short batch lays its links over the same space, which is larger (the
+    // lists hold npix counts and npix + 1 starts, and 28 bytes an event)
+    Carver sv(base);
+    w.link = sv.take<int2>(n);
+    w.tail_key = sv.take<int32_t>(n);
+    w.tail = sv.take<int32_t>(npix);
+    if (bytes) *bytes = sv.used > cv.used ? sv.used : cv.used;
     return w;
 }
 
