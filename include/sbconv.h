@@ -374,9 +374,8 @@ sbc_status sbc_conv_decay_gradient(const sbc_csr *csr, const sbc_csc *csc,
  *   Z            [n_out, P] float32 output
  * Row sums are taken in float64 in a fixed order.  The backward gives
  *   dPhi [M, P] = G~^T dZ   (float32; dZ [n_out, P] float32),
- * with the workspace of sbc_featureless_workspace_size (G~ and the split
- * partial sums of the contraction).  No pointer needs more than 4-byte
- * alignment.
+ * with the workspace of sbc_featureless_workspace_size (the blocks' parts of the
+ * product).  No pointer needs more than 4-byte alignment.
  * ------------------------------------------------------------------------ */
 size_t sbc_featureless_workspace_size(int32_t n_out, int32_t M, int32_t P);
 sbc_status sbc_featureless_forward(const sbc_csr *csr, const float *v,
