@@ -49,7 +49,7 @@ __host__ __device__ constexpr StageKind stage_kind(int32_t M, int mode) {
                                                                         : kEvents;
 }
 
-// words of a staged entry (16-byte entries stay aligned)
+// words of a staged entry
 template <int M, StageKind kKind>
 constexpr int stage_words() {
     return kKind == kCompact ? 4 : kKind == kEvents ? 1 + M / 8 : M;
@@ -98,9 +98,10 @@ __device__ __forceinline__ float4 compact_entry(const KGeo &g, int32_t i, int32_
 }
 
 // Entries a wave stages at once (entry SW weighs nothing: the slots past a
-// row's end read it).
+// row's end read it).  Compact entries move as 16 bytes, so a stage (one per
+// wave, in an array) starts and ends on 16 bytes.
 template <int M, int SW, StageKind kKind>
-struct TileStage {
+struct alignas(16) TileStage {
     static constexpr int NV = stage_words<M, kKind>();
     float v[SW + 1][NV];
     int32_t nb[SW + 1];
@@ -483,6 +484,8 @@ __global__ void __launch_bounds__(kTileThreads, 2)
     // entries loaded together: as many as the accumulators leave registers for
     constexpr int U = kTileU<M, kXbf, TR / kTileWaves, WRB * WCB * 4>;
     using Gather = TileGather<M, kXbf, kKind, T::RPW, T::SW, U>;
+    static_assert(3 * TR * T::S * 2 + kTileWaves * sizeof(typename Gather::Stage) <= 81920,
+                  "two blocks a CU");
     __shared__ __attribute__((aligned(16))) uint16_t planes[3][TR][T::S];
     __shared__ __attribute__((aligned(16))) typename Gather::Stage stage[kTileWaves];
 
@@ -614,6 +617,8 @@ __global__ void __launch_bounds__(kTileThreads, (M <= 16 ? 2 : 1))
     constexpr int NA = kXbf ? 1 : 3;  // parts of P
     constexpr int U = kTileU<M, kXbf, T::RPW, (M <= 16 ? T::MG * 2 * NPB * 4 : 64)>;
     using Gather = TileGather<M, kXbf, kKind, T::RPW, T::SW, U>;
+    static_assert((3 * T::S + NA * T::SP) * T::TR * 2 +
+                      kTileWaves * sizeof(typename Gather::Stage) <= 81920, "two blocks a CU");
     __shared__ __attribute__((aligned(16))) uint16_t dpl[3][T::TR][T::S];
     __shared__ __attribute__((aligned(16))) uint16_t ppl[NA][T::TR][T::SP];
     __shared__ __attribute__((aligned(16))) typename Gather::Stage stage[kTileWaves];
