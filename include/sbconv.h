@@ -347,10 +347,11 @@ sbc_status sbc_conv_backward(const sbc_csr *csr, const sbc_csc *csc, const float
  * kernel (Section 3.2: lambda_uv is a learned parameter):
  *     dlambda[m] = d<Y, dY>/d lambda_m = sum_e v'[e, m] f_j W_m dy_i^T,
  * v' = d p_m / d lambda_m = -dt p_m.  dW' = sum_e v'[e, :] f_j^T dy_i is
- * formed like dW of the backward: with the transpose (csc non-NULL, its
- * edge_perm may be NULL) by the fused D-route where the shape has one, else
- * as G' = N' F (the sparse product with v') and dW' = G'^T dY; then
- * dlambda[m] = <dW'_m, W_m>.  Sums are taken in a fixed order.
+ * formed like dW of the backward (with the transpose csc, whose edge_perm may
+ * be NULL, over the inputs' rows; without it over the outputs'): in one kernel
+ * with the gather where the shape has one, else as G' = N' F (the sparse
+ * product with v') and dW' = G'^T dY; then dlambda[m] = <dW'_m, W_m>.  Sums are
+ * taken in a fixed order.  dY needs no alignment beyond its elements' here.
  * geometry.basis must be SBC_BASIS_EVENT_DECAYS, M = 8 * n_decays.
  *   F [n, C_in], W [M, C_in, C_out], dY [n, C_out]  float32 or bf16 (dtype)
  *   dlambda [M]                                      float32 output

@@ -680,7 +680,7 @@ extern "C" sbc_status sbc_conv_decay_gradient(const sbc_csr *csr, const sbc_csc 
         else
             SBC_TRY(tile_weight_gradient(rows, nullptr, g, kDecayDerivMode, M, dY, F, bf, C_in,
                                          C_out, dWp, ws.part, stream, "decay_tile_dw"));
-    } else if (csc && fused_backward_available(M, C_in, C_out, bf)) {
+    } else if (csc && aligned16(dY) && fused_backward_available(M, C_in, C_out, bf)) {
         // D' = N'^T dY gathered with the derivative values, dW' = F^T D' (dF skipped)
         const int32_t np = n > csr->n_cols ? n : csr->n_cols;
         dWp = reinterpret_cast<float *>(static_cast<char *>(workspace) +

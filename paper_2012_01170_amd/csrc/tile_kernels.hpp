@@ -137,7 +137,7 @@ struct TileGather {
     int mode;
     const void *X;
     int32_t C;
-    bool vec;  // rows of X start VEC-aligned (C % VEC == 0)
+    bool vec;  // rows of X start on a load's bytes
     Stage &st;
     int lane, rl, piece;
     int32_t row_begin, wb, we, lo, hi;
@@ -146,7 +146,8 @@ struct TileGather {
 
     __device__ __forceinline__ TileGather(const TilePattern &p_, const float *v_, const KGeo &g_,
                                           int mode_, const void *X_, int32_t C_, Stage &st_)
-        : p(p_), v(v_), g(g_), mode(mode_), X(X_), C(C_), vec(C_ % VEC == 0), st(st_) {
+        : p(p_), v(v_), g(g_), mode(mode_), X(X_), C(C_),
+          vec(C_ % VEC == 0 && (reinterpret_cast<uintptr_t>(X_) & (sizeof(Raw) - 1)) == 0), st(st_) {
         lane = threadIdx.x & 63;
         rl = lane / LPR;
         piece = lane % LPR;
@@ -642,7 +643,8 @@ __global__ void __launch_bounds__(kTileThreads, (M <= 16 ? 2 : 1))
     // P rows of a tile: 8 threads a row, 2 NPB channels each
     constexpr int PV = 2 * NPB;
     const int prow = threadIdx.x >> 3, pcol = (threadIdx.x & 7) * PV;
-    const bool pvec = CP % PV == 0;
+    constexpr int PB = kXbf ? 2 * PV : 16;  // bytes of a load
+    const bool pvec = CP % PV == 0 && (reinterpret_cast<uintptr_t>(P) & (PB - 1)) == 0;
     // this XCD's contiguous range of tiles, interleaved over its blocks
     const int32_t nb = gridDim.x, xs = nb < 8 ? nb : 8;
     const int32_t x = blockIdx.x % xs, l = blockIdx.x / xs;
