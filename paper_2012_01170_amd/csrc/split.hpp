@@ -13,7 +13,8 @@
 //
 // The leading products hh are summed apart from the five others (hi and lo):
 // the small terms then keep their low bits, and an infinity or NaN among the
-// operands, whose m and l are NaN, gives what it gives in float32 (finish()).
+// operands, whose m and l are NaN, gives what it gives in float32 (finish();
+// a NaN has to be a quiet one, see quiet()).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,6 +33,13 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
     const f2 v{a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+}
+
+// x, a NaN with bit 22 set: the upper half of one whose payload lies in the
+// lower half alone reads as an infinity.  For operands as they lie in memory
+// (what arithmetic makes of a NaN has the bit).
+__device__ __forceinline__ float quiet(float x) {
+    return x == x ? x : __uint_as_float(__float_as_uint(x) | 0x00400000u);
 }
 
 // (a, b) -> their h, m and l parts, each as a word with a in the low half

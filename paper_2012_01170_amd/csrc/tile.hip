@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(256)
             const int64_t at = transposed ? ((int64_t)m * Ci + n) * Co + c
                                           : ((int64_t)m * Ci + c) * Co + n;
             if constexpr (sizeof(WT) == 2) f[j] = __uint_as_float((uint32_t)W[at] << 16);
-            else f[j] = W[at];
+            else f[j] = quiet(W[at]);
         }
     }
     uint32_t w[3][4];

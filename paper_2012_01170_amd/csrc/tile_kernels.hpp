@@ -702,7 +702,7 @@ __global__ void __launch_bounds__(kTileThreads, (M <= 16 ? 2 : 1))
             }
 #pragma unroll
             for (int k = 0; k < PV; ++k)
-                if (!on || c + k >= CP) pv[k] = 0.f;
+                pv[k] = !on || c + k >= CP ? 0.f : quiet(pv[k]);
         }
         __syncthreads();  // the previous tile is multiplied
         {

@@ -132,3 +132,35 @@ def test_tile_passes_keep_infinities(bad):
     rest[5, :] = False
     rest[:, 3] = False
     assert bool(torch.isfinite(dW[:, rest]).all())
+
+
+@pytest.mark.parametrize("bits", [0x7F800001, -0x7FFFFE, 0x7FC00000], ids=["low", "minus_low", "quiet"])
+def test_tile_passes_keep_every_nan(bits):
+    """A NaN is one by its bits: also one whose payload lies below the upper 16
+    bits, as a weight, a feature and an upstream gradient."""
+    n, ci, co = 96, 36, 20
+    idx = torch.arange(n + 1, dtype=torch.int32, device=G.DEV)
+    csr = G.sbc.CSR(idx, idx[:n].contiguous(), n, n, n)
+    csc = G.sbc.csr_transpose(csr)
+    gen = torch.Generator(device=G.DEV)
+    gen.manual_seed(6)
+    z = lambda *s: torch.rand(s, generator=gen, device=G.DEV) + 0.5
+    v = z(n, 4)
+
+    def poisoned(x, *at):
+        y = x.clone()
+        y.view(torch.int32)[at] = bits
+        assert bool(torch.isnan(y[at]))
+        return y
+
+    F, W, dY = z(n, ci), z(4, ci, co), z(n, co)
+    nan = lambda x: bool(torch.isnan(x).all())
+    Wn = poisoned(W, 2, 7, 3)
+    Y = G.sbc.conv_forward(csr, F, Wn, v=v)
+    dF, _ = G.sbc.conv_backward(csr, csc, F, Wn, dY, v=v)
+    assert nan(Y[:, 3]) and bool(torch.isfinite(Y[:, :3]).all())
+    assert nan(dF[:, 7]) and bool(torch.isfinite(dF[:, :7]).all())
+    Fn, dYn = poisoned(F, 17, 5), poisoned(dY, 40, 3)
+    Y = G.sbc.conv_forward(csr, Fn, W, v=v)
+    dF, dW = G.sbc.conv_backward(csr, csc, Fn, W, dYn, v=v)
+    assert nan(Y[17]) and nan(dF[40]) and nan(dW[:, 5, :]) and nan(dW[:, :, 3])
