@@ -1,15 +1,24 @@
 // Float32 products on the bf16 matrix cores.
 //
 // A float32 x is the exact sum of three bf16 values h + m + l (8 + 8 + 8
-// significand bits; h is x truncated, so it never overflows), and a product
-// x y is the sum of the six products hh, hm, mh, mm, hl, lh up to 2^-23 of
-// itself (ml, lm and ll are left out; their mean square is 2^-25).  Each bf16
-// product is exact in the matrix core's float32 accumulation, so a
-// contraction of split operands is as exact as one of float32 operands: K 512
-// of normal values has a relative error of 1.4e-7 with the six products summed
-// as below, 4.5e-7 by v_mfma_f32_16x16x4_f32 (measured against float64;
-// K 1024: 1.7e-7 and 5.8e-7).  Six 16x16x32 bf16 instructions take 96 cycles
-// where eight 16x16x4 float32 ones take 256 for the same products.
+// significand bits; h is x truncated, so it never overflows; the three-way
+// splitting of operands is a published method), and a product x y is the sum of
+// the six products hh, hm, mh, mm, hl, lh up to 2^-22 of itself (ml, lm and ll
+// are left out: at most 2^-22.02, where both m are near 2^-7 of their operands;
+// their mean square is 2^-25).  Each bf16 product is exact in the matrix core's
+// float32 accumulation, so over many terms a contraction of split operands is
+// closer than one of float32 operands: K 512 of normal values has a relative
+// error of 1.4e-7 with the six products summed as below, 4.5e-7 by
+// v_mfma_f32_16x16x4_f32 (measured against float64; K 1024: 1.7e-7 and 5.8e-7).
+//
+// What the split loses are tiny operands.  bf16 reaches down to 2^-133, so an
+// operand below 2^-110 keeps multiples of that only: a relative error of up to
+// 2^-134 / |x|, 2^-20 at 2^-114 (5e-35) and 2^-10 at 2^-124 (measured: 3e-7 and
+// 3e-4), where a float32 product still has 2^-24.
+//
+// Six 16x16x32 bf16 instructions take 96 cycles where eight 16x16x4 float32 ones
+// take 256 for the same products; what the pass gains from that is less, since
+// the gather and the split run beside it (tile_kernels.hpp has its times).
 //
 // The leading products hh are summed apart from the five others (hi and lo):
 // the small terms then keep their low bits, and an infinity or NaN among the

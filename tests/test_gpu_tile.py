@@ -164,3 +164,30 @@ def test_tile_passes_keep_every_nan(bits):
     Y = G.sbc.conv_forward(csr, Fn, W, v=v)
     dF, dW = G.sbc.conv_backward(csr, csc, Fn, W, dYn, v=v)
     assert nan(Y[17]) and nan(dF[40]) and nan(dW[:, 5, :]) and nan(dW[:, :, 3])
+
+
+@pytest.mark.parametrize("k", [0, 100, 114, 122])
+def test_tile_passes_on_tiny_operands(k):
+    """Operands of size 2^-k on either side: 2^-134 of an operand is lost to the
+    parts' smallest value, beside the float32 sums' 1e-6 (positive terms only,
+    so errors do not grow by cancellation)."""
+    n, ci, co = 96, 36, 20
+    idx = torch.arange(n + 1, dtype=torch.int32, device=G.DEV)
+    csr = G.sbc.CSR(idx, idx[:n].contiguous(), n, n, n)
+    csc = G.sbc.csr_transpose(csr)
+    gen = torch.Generator(device=G.DEV)
+    gen.manual_seed(7)
+    z = lambda *s: torch.rand(s, generator=gen, device=G.DEV) + 0.5
+    v = torch.ones(n, 4, device=G.DEV)
+    F, W, dY, s = z(n, ci), z(4, ci, co), z(n, co), 2.0 ** -k
+    tol = 1e-6 + 2.0 ** -134 / (0.5 * s)
+
+    def check(got, ref):
+        assert float(((got.double() - ref).abs() / ref).max()) < tol
+
+    d, Wsum = torch.float64, W.to(torch.float64).sum(0)
+    check(G.sbc.conv_forward(csr, F * s, W, v=v), (F * s).to(d) @ Wsum)
+    check(G.sbc.conv_forward(csr, F, W * s, v=v), F.to(d) @ (Wsum * s))
+    dF, dW = G.sbc.conv_backward(csr, csc, F, W, dY * s, v=v)
+    check(dF, (dY * s).to(d) @ Wsum.t().contiguous())
+    check(dW[1], F.to(d).t().contiguous() @ (dY * s).to(d))
