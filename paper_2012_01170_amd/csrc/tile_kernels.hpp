@@ -97,6 +97,11 @@ __device__ __forceinline__ float4 compact_entry(const KGeo &g, int32_t i, int32_
     return make_float4((float)ux, (float)uy, (float)uz, (float)w);
 }
 
+// row0 + up, at most n_rows (the sum may pass 2^31)
+__host__ __device__ constexpr int32_t row_at(int32_t row0, int32_t up, int32_t n_rows) {
+    return row0 < n_rows - up ? row0 + up : n_rows;
+}
+
 // Entries a wave stages at once (entry SW weighs nothing: the slots past a
 // row's end read it).  Compact entries move as 16 bytes, so a stage (one per
 // wave, in an array) starts and ends on 16 bytes.
@@ -157,9 +162,7 @@ struct TileGather {
     // row bounds of the wave's rows (clamped into [0, nnz])
     __device__ __forceinline__ void begin(int32_t row0) {
         row_begin = row0;
-        int32_t r = row0 + (lane < RPW ? lane : RPW);
-        r = r < p.n_rows ? r : p.n_rows;
-        const int32_t b = p.ptr[r];
+        const int32_t b = p.ptr[row_at(row0, lane < RPW ? lane : RPW, p.n_rows)];
         bound = b < 0 ? 0 : (b < g.nnz ? b : g.nnz);
         wb = __builtin_amdgcn_readlane(bound, 0);
         we = __builtin_amdgcn_readlane(bound, RPW);

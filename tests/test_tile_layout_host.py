@@ -41,3 +41,17 @@ static_assert(whole<8, DwShape<8, 4, kCompact>::SW>(), "M 8, weight gradient");
 static_assert(whole<10, DwShape<10, 4, kCompact>::SW>(), "M 10, weight gradient");
 """)
     assert r.returncode == 0, r.stderr
+
+
+@needs_hipcc
+def test_row_bounds_stay_in_range(tmp_path):
+    """The row pointer a lane reads, up to the last rows of the largest pattern
+    (in a constant expression an overflow of int32 is an error)."""
+    r = host_compile(tmp_path, """
+constexpr int32_t n = 2147483647;
+static_assert(row_at(0, 0, 1) == 0 && row_at(0, 1, 1) == 1 && row_at(0, 16, 1) == 1, "one row");
+static_assert(row_at(48, 16, 65) == 64 && row_at(64, 16, 65) == 65, "a ragged tile");
+static_assert(row_at(n - 15, 16, n) == n && row_at(n - 63 + 48, 16, n) == n, "the last tile");
+static_assert(row_at(n - 16, 15, n) == n - 1 && row_at(n, 16, n) == n, "the last row");
+""")
+    assert r.returncode == 0, r.stderr
