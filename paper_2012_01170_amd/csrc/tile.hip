@@ -99,13 +99,14 @@ __global__ void __launch_bounds__(256)
     else dW[((int64_t)m * CQ + q) * CP + c] = t;
 }
 
-// Rows per tile: 64 where the tiles then still give two blocks per CU (half the
-// weight bytes per row), else 32; 32 where a wave's sums of 64 rows leave no
-// registers for the products (M > 10, and M = 10 with more than 64 columns).
-int contract_tr(int32_t M, int32_t n_rows, int32_t N) {
-    if (M > 10 || (M == 10 && N > 64)) return 32;
+// Whether tiles of 64 rows are taken where the rows are short (half the weight
+// bytes per row): the tiles then still give two blocks per CU, and a wave's sums
+// of 64 rows leave registers for the products (not for M > 10, nor for M = 10
+// with more than 64 columns).
+bool contract_tall(int32_t M, int32_t n_rows, int32_t N) {
+    if (M > 10 || (M == 10 && N > 64)) return false;
     const int32_t chunks = (N + 127) / 128;
-    return (int64_t)(n_rows + 63) / 64 * chunks >= 512 ? 64 : 32;
+    return ((int64_t)n_rows + 63) / 64 * chunks >= 512;
 }
 
 int32_t dw_splits(int32_t n_rows, int32_t M, int32_t CP, int32_t CQ) {
@@ -134,7 +135,6 @@ sbc_status tile_contract(const TilePattern &p, const float *v, const KGeo &g, in
                          int32_t N, float *out, void *frag, hipStream_t stream,
                          const char *trace) {
     if (p.n_rows <= 0) return SBC_OK;
-    const int tr = contract_tr(M, p.n_rows, N);
     const int32_t slices = (C + kTileCS - 1) / kTileCS;
     const int32_t Ci = w_transposed ? N : C, Co = w_transposed ? C : N;
     const int64_t lanes = (int64_t)slices * M * ((N + 15) / 16) * 64;
@@ -149,7 +149,8 @@ sbc_status tile_contract(const TilePattern &p, const float *v, const KGeo &g, in
                            stream, static_cast<const float *>(W), M, Ci, Co, w_transposed, slices,
                            fr);
     SBC_LAUNCH_CHECK();
-    const TileContractArgs a{p, v, g, mode, X, C, fr, N, out, tr};
+    const TileContractArgs a{p, v, g, mode, X, C, fr, N, out,
+                             contract_tall(M, p.n_rows, N)};
     SBC_TRY(M <= 10 ? launch_contract_4_8_10(M, bf16, a, stream)
                     : launch_contract_16_24_32(M, bf16, a, stream));
     trace_after(trace, stream);

@@ -16,7 +16,7 @@ struct TileContractArgs {
     const uint16_t *frag;
     int32_t N;
     float *out;
-    int tr;  // rows per tile: 64 (M <= 10 only) or 32
+    bool tall;  // tiles of 64 rows where the rows are short (M <= 10 only)
 };
 
 struct TileDwArgs {

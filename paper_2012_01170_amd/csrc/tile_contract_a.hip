@@ -6,12 +6,12 @@ namespace sbc {
 
 template <int M, StageKind kKind>
 static void launch_p(bool bf16, const TileContractArgs &a, hipStream_t s) {
-    if (a.tr == 64) {
-        if (bf16) launch_contract<M, true, kKind, 64>(a, s);
-        else launch_contract<M, false, kKind, 64>(a, s);
+    if (a.tall) {
+        if (bf16) launch_contract<M, true, kKind, true>(a, s);
+        else launch_contract<M, false, kKind, true>(a, s);
     } else {
-        if (bf16) launch_contract<M, true, kKind, 32>(a, s);
-        else launch_contract<M, false, kKind, 32>(a, s);
+        if (bf16) launch_contract<M, true, kKind, false>(a, s);
+        else launch_contract<M, false, kKind, false>(a, s);
     }
 }
 

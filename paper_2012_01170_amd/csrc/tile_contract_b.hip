@@ -6,11 +6,11 @@ namespace sbc {
 template <int M>
 static void launch_m(bool bf16, const TileContractArgs &a, hipStream_t s) {
     if (stage_kind(M, a.mode) == kEvents) {
-        if (bf16) launch_contract<M, true, kEvents, 32>(a, s);
-        else launch_contract<M, false, kEvents, 32>(a, s);
+        if (bf16) launch_contract<M, true, kEvents, false>(a, s);
+        else launch_contract<M, false, kEvents, false>(a, s);
     } else {
-        if (bf16) launch_contract<M, true, kValues, 32>(a, s);
-        else launch_contract<M, false, kValues, 32>(a, s);
+        if (bf16) launch_contract<M, true, kValues, false>(a, s);
+        else launch_contract<M, false, kValues, false>(a, s);
     }
 }
 

@@ -471,33 +471,43 @@ struct TileShape {
     static_assert(SW >= 64, "a stage of at least 64 entries");
 };
 
+// LDS of a tile: the planes of four basis functions' columns, then the stages.
+template <int M, bool kXbf, StageKind kKind, int TR, int NCBW, int WCB>
+struct ContractTile {
+    using T = TileShape<M, TR, kKind>;
+    static constexpr int WRB = TR / 16 / (kTileWaves / NCBW);
+    // entries loaded together: as many as the accumulators leave registers for
+    static constexpr int U = kTileU<M, kXbf, TR / kTileWaves, WRB * WCB * 4>;
+    using Gather = TileGather<M, kXbf, kKind, T::RPW, T::SW, U>;
+    static constexpr int plane_bytes = 3 * TR * T::S * 2;
+    static constexpr int bytes = plane_bytes + kTileWaves * (int)sizeof(typename Gather::Stage);
+    static_assert(plane_bytes % 16 == 0 && bytes <= 81920, "aligned stages, two blocks a CU");
+};
+
 // out tile [TR, 16 NCBW WCB] of columns from blockIdx.y's chunk.  Waves:
 // NCBW column groups x 4 / NCBW row groups, each WCB column blocks (16 NCBW
 // columns apart) and WRB row blocks.  B comes as fragments (tile_frag_kernel)
-// straight from L2, 6 M C N bytes for every TR rows, hence 64 rows where they
-// fill the chip.  The second block of the CU covers this one's gather.
+// straight from L2, 6 M C N bytes for every TR rows.  The second block of the
+// CU covers this one's gather.
 template <int M, bool kXbf, StageKind kKind, int TR, int NCBW, int WCB>
-__global__ void __launch_bounds__(kTileThreads, 2)
-    tile_contract_kernel(TilePattern p, const float *__restrict__ v, KGeo g, int mode,
-                         const void *__restrict__ X, int32_t C,
-                         const uint16_t *__restrict__ frag, int32_t N, float *__restrict__ out) {
-    using T = TileShape<M, TR, kKind>;
+__device__ __forceinline__ void contract_tile(char *lds, int32_t row0, const TilePattern &p,
+                                              const float *__restrict__ v, const KGeo &g, int mode,
+                                              const void *__restrict__ X, int32_t C,
+                                              const uint16_t *__restrict__ frag, int32_t N,
+                                              float *__restrict__ out) {
+    using CT = ContractTile<M, kXbf, kKind, TR, NCBW, WCB>;
+    using T = typename CT::T;
+    using Gather = typename CT::Gather;
     constexpr int NRG = kTileWaves / NCBW;
-    constexpr int WRB = TR / 16 / NRG;
+    constexpr int WRB = CT::WRB;
     constexpr int NB = kXbf ? 1 : 3;
-    // entries loaded together: as many as the accumulators leave registers for
-    constexpr int U = kTileU<M, kXbf, TR / kTileWaves, WRB * WCB * 4>;
-    using Gather = TileGather<M, kXbf, kKind, T::RPW, T::SW, U>;
-    static_assert(3 * TR * T::S * 2 + kTileWaves * sizeof(typename Gather::Stage) <= 81920,
-                  "two blocks a CU");
-    __shared__ __attribute__((aligned(16))) uint16_t planes[3][TR][T::S];
-    __shared__ __attribute__((aligned(16))) typename Gather::Stage stage[kTileWaves];
+    auto planes = reinterpret_cast<uint16_t(*)[TR][T::S]>(lds);
+    auto stage = reinterpret_cast<typename Gather::Stage *>(lds + CT::plane_bytes);
 
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     const int lr = lane >> 4, lc = lane & 15;
     const int wc = w % NCBW, wr = w / NCBW;
-    const int32_t row0 = tile_of_block(blockIdx.x, gridDim.x) * TR;
     const int32_t ncb = (N + 15) / 16;
     const int32_t cb0 = blockIdx.y * NCBW * WCB;
     const int32_t slices = (C + Gather::CS - 1) / Gather::CS;
@@ -578,6 +588,54 @@ __global__ void __launch_bounds__(kTileThreads, 2)
                 if (row < p.n_rows && col < N) out[(int64_t)row * N + col] = sum[u][t][r];
             }
         }
+}
+
+// Most entries a row, in the mean, for which tiles of 64 rows are taken: they
+// halve the weights' bytes per row, but a wave then gathers 16 rows by pieces of
+// 64 bytes, where 8 rows take whole lines of 128.  128 clouds of 1024, 64 -> 64,
+// 64 rows against 32: M 8, 5 entries a row 99 and 127 us, 16: 187 and 182, 45:
+// 526 and 429; values given, 16: 226 and 174.  Three parts of the weights for
+// more than 64 columns weigh more (16 entries: 218 and 218).  Event entries are
+// shorter to gather, and their rows' lengths differ more: 64 rows throughout
+// (300k events, 14 entries: 305 and 309; 64 -> 128, 373 and 450).
+template <bool kXbf, int COLS>
+constexpr int kTallEntries = !kXbf && COLS > 64 ? 16 : 10;
+template <StageKind kKind>
+constexpr bool kAlwaysTall = kKind == kEvents;
+
+// kTall: tiles of 64 rows, or where there is a choice the pattern's own entry
+// count (the host knows a bound alone) decides between 64 and 32 rows; the grid
+// is that of 32 then, and the blocks past the last tile of 64 end at once.
+template <int M, bool kXbf, StageKind kKind, bool kTall, int NCBW, int WCB>
+__global__ void __launch_bounds__(kTileThreads, 2)
+    tile_contract_kernel(TilePattern p, const float *__restrict__ v, KGeo g, int mode,
+                         const void *__restrict__ X, int32_t C,
+                         const uint16_t *__restrict__ frag, int32_t N, float *__restrict__ out) {
+    using Low = ContractTile<M, kXbf, kKind, 32, NCBW, WCB>;
+    if constexpr (kTall && kAlwaysTall<kKind>) {
+        __shared__ __attribute__((aligned(16))) char
+            lds[ContractTile<M, kXbf, kKind, 64, NCBW, WCB>::bytes];
+        contract_tile<M, kXbf, kKind, 64, NCBW, WCB>(lds, tile_of_block(blockIdx.x, gridDim.x) * 64,
+                                                     p, v, g, mode, X, C, frag, N, out);
+    } else if constexpr (kTall) {
+        using Tall = ContractTile<M, kXbf, kKind, 64, NCBW, WCB>;
+        __shared__ __attribute__((aligned(16))) char
+            lds[Tall::bytes > Low::bytes ? Tall::bytes : Low::bytes];
+        const int64_t entries = p.ptr[p.n_rows];
+        if (entries <= (int64_t)kTallEntries<kXbf, 16 * NCBW * WCB> * p.n_rows) {
+            const int32_t tiles = p.n_rows / 64 + (p.n_rows % 64 != 0);
+            if ((int32_t)blockIdx.x < tiles)
+                contract_tile<M, kXbf, kKind, 64, NCBW, WCB>(
+                    lds, tile_of_block(blockIdx.x, tiles) * 64, p, v, g, mode, X, C, frag, N, out);
+            return;
+        }
+        contract_tile<M, kXbf, kKind, 32, NCBW, WCB>(lds, tile_of_block(blockIdx.x, gridDim.x) * 32,
+                                                     p, v, g, mode, X, C, frag, N, out);
+    } else {
+        __shared__ __attribute__((aligned(16))) char lds[Low::bytes];
+        contract_tile<M, kXbf, kKind, 32, NCBW, WCB>(lds, tile_of_block(blockIdx.x, gridDim.x) * 32,
+                                                     p, v, g, mode, X, C, frag, N, out);
+    }
 }
 
 // ---------------------------------------------------------------- weight gradient

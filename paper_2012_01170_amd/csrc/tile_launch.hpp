@@ -6,19 +6,22 @@
 
 namespace sbc {
 
-template <int M, bool kXbf, StageKind kKind, int TR>
+// Columns a block takes: N rounded up to 32, 64 or 128.
+inline int32_t contract_columns(int32_t N) { return N <= 32 ? 32 : N <= 64 ? 64 : 128; }
+
+template <int M, bool kXbf, StageKind kKind, bool kTall>
 void launch_contract(const TileContractArgs &a, hipStream_t s) {
-    const int32_t ncb = (a.N + 15) / 16;
-    const unsigned tiles = (unsigned)grid_for(a.p.n_rows, TR);
+    const int32_t tiles = grid_for(a.p.n_rows, kTall && kAlwaysTall<kKind> ? 64 : 32);
+    const int32_t cols = contract_columns(a.N);
 #define SBC_TILE(NCBW, WCB)                                                                      \
-    hipLaunchKernelGGL((tile_contract_kernel<M, kXbf, kKind, TR, NCBW, WCB>),                            \
-                       dim3(tiles, (unsigned)((ncb + NCBW * WCB - 1) / (NCBW * WCB))),            \
-                       dim3(kTileThreads), 0, s, a.p, a.v, a.g, a.mode, a.X, a.C, a.frag, a.N,    \
+    hipLaunchKernelGGL((tile_contract_kernel<M, kXbf, kKind, kTall, NCBW, WCB>),                 \
+                       dim3((unsigned)tiles, (unsigned)((a.N + cols - 1) / cols)),               \
+                       dim3(kTileThreads), 0, s, a.p, a.v, a.g, a.mode, a.X, a.C, a.frag, a.N,   \
                        a.out)
-    // column blocks of 16 over the waves: the fewest that cover N, 128 at most
-    if (ncb <= 2) SBC_TILE(2, 1);
-    else if (ncb <= 4) SBC_TILE(2, 2);
-    else if constexpr (M < 10 || TR == 32) SBC_TILE(4, 2);
+    // (column blocks of 16 over the waves)
+    if (cols == 32) SBC_TILE(2, 1);
+    else if (cols == 64) SBC_TILE(2, 2);
+    else if constexpr (M < 10 || !kTall) SBC_TILE(4, 2);
 #undef SBC_TILE
 }
 

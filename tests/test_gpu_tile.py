@@ -191,3 +191,56 @@ def test_tile_passes_on_tiny_operands(k):
     dF, dW = G.sbc.conv_backward(csr, csc, F, W, dY * s, v=v)
     check(dF, (dY * s).to(d) @ Wsum.t().contiguous())
     check(dW[1], F.to(d).t().contiguous() @ (dY * s).to(d))
+
+
+# Patterns of two blocks of 64 rows per CU and more, where the mean number of
+# entries chooses the tile's height (10 a row, 16 for float32 and more than 64
+# columns; event bases: 64 rows always): (rows short, workload).
+_BIG = dict(n_clouds=33, n=1000, radius=0.5)
+TALL = {
+    "f32_short": (True, lambda: P(seed=90, k_cap=6, c_in=20, c_out=33, **_BIG)),
+    "f32_long": (False, lambda: P(seed=90, k_cap=14, c_in=20, c_out=33, **_BIG)),
+    "f32_ten": (True, lambda: P(seed=91, k_cap=10, c_in=12, c_out=12, **_BIG)),
+    "f32_eleven": (False, lambda: P(seed=91, k_cap=11, c_in=12, c_out=12, **_BIG)),
+    "f32_wide_short": (True, lambda: P(seed=92, k_cap=14, c_in=36, c_out=72, **_BIG)),
+    "f32_wide_long": (False, lambda: P(seed=92, k_cap=18, c_in=36, c_out=72, **_BIG)),
+    "bf16_pieces_short": (True, lambda: P(seed=93, k_cap=5, c_in=40, c_out=24, dtype="bf16", **_BIG)),
+    "bf16_pieces_long": (False, lambda: P(seed=93, k_cap=13, c_in=40, c_out=24, dtype="bf16", **_BIG)),
+    "bf16_odd_wide_short": (True, lambda: P(seed=94, k_cap=5, c_in=21, c_out=70, dtype="bf16", **_BIG)),
+    "bf16_odd_wide_long": (False, lambda: P(seed=94, k_cap=12, c_in=21, c_out=70, dtype="bf16", **_BIG)),
+    "weighted_short": (True, lambda: P(seed=95, k_cap=5, c_in=16, c_out=64,
+                                       basis=workloads.BASIS_WMONO10, **_BIG)),
+    "weighted_long": (False, lambda: P(seed=95, k_cap=12, c_in=16, c_out=64,
+                                       basis=workloads.BASIS_WMONO10, **_BIG)),
+    "mono4_long": (False, lambda: P(seed=96, k_cap=15, c_in=68, c_out=17,
+                                    basis=workloads.BASIS_MONO4, **_BIG)),
+    "events": (None, lambda: E(seed=97, n=33000, width=128, height=96, c=48)),
+    "events_bf16_wide": (None, lambda: E(seed=98, n=33000, width=96, height=96, c=72, dtype="bf16")),
+    "events_long": (None, lambda: E(seed=99, n=33000, width=64, height=40, c=20)),
+}
+
+
+@pytest.mark.parametrize("name", list(TALL))
+def test_tile_height(name):
+    short, make = TALL[name]
+    w = make()
+    print(f"[tile height] {name}", flush=True)
+    rp, ci, v = _pattern(w)
+    mean = len(ci) / w["n_out"]
+    assert w["n_out"] // 64 >= 512
+    wide = w["dtype"] == "f32" and w["C_out"] > 64
+    if short is not None:
+        assert short == (mean <= (16 if wide else 10))
+    t = G.to_device(w)
+    csr = G.search(w, t)
+    geo = G.geometry(w, t)
+    csc = G.sbc.csr_transpose(csr)
+    Y_ref = oracle.conv.forward(rp, ci, v, w["F"], w["W"])
+    dF_ref, dW_ref = oracle.conv.backward(rp, ci, v, w["F"], w["W"], w["dY"], w["n_in"])
+    vd = torch.from_numpy(np.ascontiguousarray(v, dtype=np.float32)).to(G.DEV)
+    for geometry, values in ((geo, None), (None, vd)):
+        Y = G.sbc.conv_forward(csr, t["F"], t["W"], geometry=geometry, v=values)
+        dF, dW = G.sbc.conv_backward(csr, csc, t["F"], t["W"], t["dY"], geometry=geometry, v=values)
+        assert G.row_error(Y.cpu().numpy(), Y_ref) < G.TOL_F32
+        assert G.row_error(dF.cpu().numpy(), dF_ref) < G.TOL_F32
+        assert G.norm_error(dW.cpu().numpy(), dW_ref) < G.TOL_F32
