@@ -244,3 +244,23 @@ def test_tile_height(name):
         assert G.row_error(Y.cpu().numpy(), Y_ref) < G.TOL_F32
         assert G.row_error(dF.cpu().numpy(), dF_ref) < G.TOL_F32
         assert G.norm_error(dW.cpu().numpy(), dW_ref) < G.TOL_F32
+
+
+@pytest.mark.parametrize("n,c_out", [(40, 128), (40, 33), (2048, 128), (4096, 128), (4160, 128),
+                                     (8192, 64), (8193, 64), (300, 300)])
+def test_tile_columns(n, c_out):
+    """Blocks of 32, 64 and 128 columns, chosen by the rows: every column of
+    every row, last blocks included."""
+    print(f"[tile columns] {n} {c_out}", flush=True)
+    w = P(seed=70, n_clouds=1, n=n, radius=0.3, k_cap=5, c_in=9, c_out=c_out)
+    rp, ci, v = _pattern(w)
+    t = G.to_device(w)
+    csr = G.search(w, t)
+    csc = G.sbc.csr_transpose(csr)
+    Y = G.sbc.conv_forward(csr, t["F"], t["W"], geometry=G.geometry(w, t))
+    assert G.row_error(Y.cpu().numpy(), oracle.conv.forward(rp, ci, v, w["F"], w["W"])) < G.TOL_F32
+    # the input gradient of the reversed layer has the same columns
+    dF, _ = G.sbc.conv_backward(csr, csc, t["dY"], t["W"].transpose(1, 2).contiguous(), t["F"],
+                                geometry=G.geometry(w, t), need_dW=False)
+    dF_ref, _ = oracle.conv.backward(rp, ci, v, w["dY"], w["W"].transpose(0, 2, 1), w["F"], n)
+    assert G.row_error(dF.cpu().numpy(), dF_ref) < G.TOL_F32
