@@ -1223,7 +1223,7 @@ template <int M, int CI, int CO, bool kBf>
 constexpr bool reg_forward_fits() {
     // float32 rows wider than 32 channels hold M*CI/4 gather accumulators per
     // lane and spend long on float32 MFMAs with two waves per SIMD; there the
-    // tile pass is faster.  bf16 rows of 64 channels still gain.
+    // LDS-tile kernel is faster.  bf16 rows of 64 channels still gain.
     return reg_w_bytes<M, CI, CO, kBf>() <= 131072 && CI % 16 == 0 &&
            (CI <= 32 || (kBf && CI <= 64)) && CO % 16 == 0 && (!kBf || (CI / 4) % 8 == 0);
 }
@@ -1233,14 +1233,6 @@ constexpr bool reg_forward_fits() {
 template <int M, int CI>
 constexpr int reg_waves_per_eu() {
     return M * CI / 4 <= 64 ? 4 : 2;
-}
-
-// Whether the forward loads a step ahead (below): learned decays in float32 at
-// two waves a SIMD.  (bf16 rows of 64 channels with the fixed decay took the
-// same 319 us with it and without.)
-template <int M, int CI, int kBasis, bool kBf>
-constexpr bool reg_ahead() {
-    return M * CI / 4 > 64 && !kBf && kBasis == SBC_BASIS_EVENT_DECAYS + 1;
 }
 
 template <int M, int CI, int CO, int kBasis, bool kBf>
@@ -1321,75 +1313,6 @@ __global__ void __launch_bounds__(kRegWaves * 64)
 #pragma unroll
             for (int t = 0; t < CG; ++t) acc[m][t] = 0.f;
 
-        if constexpr (reg_ahead<M, CI, kBasis, kBf>()) {
-            // With 128 sums a lane two waves a SIMD leave every step's loads
-            // exposed: the features and the coordinates of a step are loaded
-            // during the step before (the indices two before), into two
-            // register sets in turn, and the group shares an edge's offset and
-            // its decays instead of its M values.  300k events, two decays, 32
-            // -> 32: 264 -> 248 us.
-            constexpr int Mv = M / 8;
-            constexpr int NR = CG / 4;  // 16-byte pieces an edge
-            struct Step {
-                u32x4 f[4][NR];
-                int4 ev;
-            };
-            const int4 a = g.ev[row < n_out ? row : 0];
-            auto index = [&](int32_t e, int32_t last) { return e < e1 ? col_idx[e] : last; };
-            // (past the row's end a lane reads its last neighbour again, with no weight)
-            auto fetch = [&](int32_t j, Step &st) {
-                st.ev = g.ev[j];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int32_t ju = __shfl(j, rl + 16 * u, 64);
-                    const u32x4 *src = reinterpret_cast<const u32x4 *>(
-                        static_cast<const float *>(Fv) + (int64_t)ju * CI + gq * CG);
-#pragma unroll
-                    for (int c = 0; c < NR; ++c) st.f[u][c] = src[c];
-                }
-            };
-            auto add = [&](int32_t e, const Step &st) {
-                int k = event_index(a.x - st.ev.x, a.y - st.ev.y);
-                const float dt = (float)((int64_t)a.z - (int64_t)st.ev.z);
-                float x[Mv];
-#pragma unroll
-                for (int q = 0; q < Mv; ++q)
-                    x[q] = expf(-g.decays[(k >= 0 ? k : 0) * Mv + q] * dt);
-                if (e >= e1) k = -1;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int ku = __shfl(k, rl + 16 * u, 64);
-                    float xu[Mv], f[CG];
-#pragma unroll
-                    for (int q = 0; q < Mv; ++q) xu[q] = __shfl(x[q], rl + 16 * u, 64);
-#pragma unroll
-                    for (int t = 0; t < CG; ++t) f[t] = piece_elem<false>(st.f[u][t / 4], t % 4);
-#pragma unroll
-                    for (int m = 0; m < M; ++m) {
-                        const float bm = ku == m / Mv ? xu[m % Mv] : 0.f;
-#pragma unroll
-                        for (int t = 0; t < CG; ++t) acc[m][t] += bm * f[t];
-                    }
-                }
-            };
-            Step s0, s1;
-            const int32_t j0 = index(e0 + gq, 0);
-            int32_t j1 = index(e0 + 4 + gq, j0);
-            fetch(j0, s0);
-#pragma unroll 1
-            for (int32_t q = 0; q < len; q += 8) {
-                const int32_t e = e0 + q + gq;
-                fetch(j1, s1);
-                const int32_t j2 = index(e + 8, j1);
-                __builtin_amdgcn_sched_barrier(0);
-                add(e, s0);
-                if (q + 4 >= len) break;
-                fetch(j2, s0);
-                j1 = index(e + 12, j2);
-                __builtin_amdgcn_sched_barrier(0);
-                add(e + 4, s1);
-            }
-        } else {
         // Four edges of the row per step, one per lane of the row's group:
         // lane gq loads the neighbour index of edge q + gq one step ahead and
         // evaluates that edge's basis; the group shares indices and basis
@@ -1456,7 +1379,6 @@ __global__ void __launch_bounds__(kRegWaves * 64)
                     for (int t = 0; t < CG; ++t) acc[m][t] += bm * f[us][t];
                 }
             }
-        }
         }
 
         // ---- Y rows of the tile = G W on the matrix cores
