@@ -187,7 +187,7 @@ size_t route_bytes(Route r, int32_t n_out, int32_t n_in, int64_t nnz, int32_t M,
     if (route_fused(r, M, Ci, Co, bf))
         return r == kFwdSpmm
                    ? fused_forward_workspace_bytes(n_out > n_in ? n_out : n_in)
-                   : fused_workspace_bytes(M, Ci, Co, n_out > n_in ? n_out : n_in, nnz);
+                   : fused_workspace_bytes(M, Ci, Co, n_out > n_in ? n_out : n_in);
     size_t b = 0;
     carve_route(nullptr, r, n_out, n_in, nnz, M, Ci, Co, &b);
     return b;
@@ -638,7 +638,7 @@ extern "C" size_t sbc_decay_gradient_workspace_size(int32_t n, int64_t nnz_bound
     }
     carve_decay(nullptr, n, nnz_bound, M, C_in, C_out, &bytes);
     // the fused D-route: its own workspace, then dW'
-    const size_t fused = fused_workspace_bytes(M, C_in, C_out, n, nnz_bound) +
+    const size_t fused = fused_workspace_bytes(M, C_in, C_out, n) +
                          align_up((size_t)M * C_in * C_out * 4);
     return fused_backward_available(M, C_in, C_out, dtype == SBC_BF16) && fused > bytes ? fused
                                                                                         : bytes;
@@ -684,7 +684,7 @@ extern "C" sbc_status sbc_conv_decay_gradient(const sbc_csr *csr, const sbc_csc 
         // D' = N'^T dY gathered with the derivative values, dW' = F^T D' (dF skipped)
         const int32_t np = n > csr->n_cols ? n : csr->n_cols;
         dWp = reinterpret_cast<float *>(static_cast<char *>(workspace) +
-                                        fused_workspace_bytes(M, C_in, C_out, np, csr->nnz_bound));
+                                        fused_workspace_bytes(M, C_in, C_out, np));
         SBC_TRY(fused_backward(csr, csc, nullptr, geometry, M, F, W, dY, bf, C_in, C_out, nullptr,
                                dWp, workspace, stream, true));
     } else {

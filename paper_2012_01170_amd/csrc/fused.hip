@@ -130,18 +130,16 @@ __device__ __forceinline__ int32_t load_bound(const int32_t *__restrict__ ptr, i
 //   X [*, C] features gathered along the pattern; out tile row stride S
 //   (elements), row r_local at out + r_local * S, column m*C + c.
 //   pre.bound: load_bound<RPW>(ptr, n_rows, row_begin) of this lane;
-//   pre.idx0 (pre.have_idx, pipelined only): idx[first edge + lane].
-//   next_row_begin >= 0: the bound of the next call's rows (and, pipelined,
-//   its first neighbour indices) is loaded while this one runs and returned.
+//   pre.idx0 (pre.have_idx): idx[first edge + lane].
+//   next_row_begin >= 0: the bound of the next call's rows and its first
+//   neighbour indices are loaded while this one runs and returned.
 // The wave's edges are staged 64 at a time; the rows are owned by groups of
 // LPR lanes (each group owns NB rows, all accumulators live across the
-// staging chunks).  kPipelined: the group's NB rows advance together with
-// NB * U feature loads in flight, and the first feature loads of a chunk are
-// issued together with the coordinate loads of the chunk's basis values, so
-// they share one memory round trip (for persistent waves that gather while
-// other waves multiply).  Otherwise the rows are taken one after another,
-// four edges at a time, after the basis values (for blocks that gather and
-// then multiply, where the co-resident block hides the latency).
+// staging chunks).  The group's NB rows advance together with NB * U feature
+// loads in flight, and the first feature loads of a chunk are issued together
+// with the coordinate loads of the chunk's basis values, so they share one
+// memory round trip (for persistent waves that gather while other waves
+// multiply).
 // What a gather call hands to the next one: the next rows' bound for this
 // lane and, when known, the neighbour index of the lane's edge in the next
 // rows' first chunk.
@@ -151,7 +149,7 @@ struct GatherAhead {
     bool have_idx;
 };
 
-template <int M, int C, int kBasis, bool kXbf, bool kOutBf, bool kT, int RPW, bool kPipelined>
+template <int M, int C, int kBasis, bool kXbf, bool kOutBf, bool kT, int RPW>
 __device__ __forceinline__ GatherAhead gather_rows(int32_t row_begin, int32_t n_rows,
                                                    const int32_t *__restrict__ ptr,
                                                    const int32_t *__restrict__ idx,
@@ -169,15 +167,13 @@ __device__ __forceinline__ GatherAhead gather_rows(int32_t row_begin, int32_t n_
     constexpr int RPB_ = 64 / LPR;
     constexpr int RPB = RPB_ < RPW ? RPB_ : RPW;   // rows in flight at once
     constexpr int NB = (RPW + RPB - 1) / RPB;      // rows per lane group
-    // pipelined, with fewer rows than lane groups: SPL groups share a row,
+    // with fewer rows than lane groups SPL groups share a row,
     // group part p taking its edges rs + p, rs + p + SPL, ...; the partial
     // sums are added across the groups at the end
-    constexpr int SPL = (kPipelined && RPB_ > RPW) ? RPB_ / RPW : 1;
+    constexpr int SPL = RPB_ > RPW ? RPB_ / RPW : 1;
     // edges per row loaded together: NB * U feature loads (16 bytes each, 32
-    // registers in all) in flight per lane (pipelined), or 4 per row with the
-    // rows taken one after another
-    constexpr int UP = 8 / NB > 1 ? 8 / NB : 1;
-    constexpr int U = kPipelined ? UP : 4;
+    // registers in all) in flight per lane
+    constexpr int U = 8 / NB > 1 ? 8 / NB : 1;
     const int lane = threadIdx.x & 63;
     const int slot = lane / LPR;
     const int cg = lane % LPR;
@@ -216,52 +212,10 @@ __device__ __forceinline__ GatherAhead gather_rows(int32_t row_begin, int32_t n_
             for (int q = 1; q < RPW; ++q)
                 if (st.bounds[q] <= e) s = q;
             row = row_begin + s;
-            other = (kPipelined && pre.have_idx && c0 == wb) ? pre.idx0 : idx[e];
+            other = (pre.have_idx && c0 == wb) ? pre.idx0 : idx[e];
             ev = (kBasis == 0) ? (perm ? (int64_t)perm[e] : (int64_t)e) : 0;
             st.nb[lane] = other;
             if (lane == 0) st.nb[64] = other;  // padding edge: a valid row, weight 0
-        }
-        if constexpr (!kPipelined) {
-            // basis values first, then each row of the lane group in turn
-            if (e < we) {
-                float bv[M];
-                if (kT)
-                    edge_basis<M, kBasis>(g, v, other, row, ev, inv_r, inv_tau, bv);
-                else
-                    edge_basis<M, kBasis>(g, v, row, other, ev, inv_r, inv_tau, bv);
-#pragma unroll
-                for (int m = 0; m < M; ++m) st.v[lane][m] = bv[m];
-                if (lane == 0) {
-#pragma unroll
-                    for (int m = 0; m < M; ++m) st.v[64][m] = 0.f;
-                }
-            }
-            wave_lds_sync();
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int32_t lo = rs[b] > c0 ? rs[b] : c0;
-                const int32_t hi = re[b] < c0 + 64 ? re[b] : c0 + 64;
-#pragma unroll 1
-                for (int32_t e2 = lo; e2 < hi; e2 += U) {
-                    float f[U][VEC];
-                    int q[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        q[u] = e2 + u < hi ? e2 + u - c0 : 64;
-                        load_row_vec<C, VEC, kXbf>(Xv, st.nb[q[u]], cg, f[u]);
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int m = 0; m < M; ++m) {
-                            const float vm = st.v[q[u]][m];
-#pragma unroll
-                            for (int k = 0; k < VEC; ++k) acc[b][m][k] += vm * f[u][k];
-                        }
-                }
-            }
-            wave_lds_sync();
-            continue;
         }
         wave_lds_sync();
         // the lane group's NB rows advance together, U edges each per step
@@ -356,7 +310,7 @@ __device__ __forceinline__ GatherAhead gather_rows(int32_t row_begin, int32_t n_
         }
     }
     GatherAhead ahead{next_bound, 0, false};
-    if (kPipelined && next_row_begin >= 0) {
+    if (next_row_begin >= 0) {
         const int32_t nb0 = __shfl(next_bound, 0, 64), nb1 = __shfl(next_bound, RPW, 64);
         ahead.idx0 = nb0 + lane < nb1 ? idx[nb0 + lane] : 0;
         ahead.have_idx = true;
@@ -1223,7 +1177,7 @@ template <int M, int CI, int CO, bool kBf>
 constexpr bool reg_forward_fits() {
     // float32 rows wider than 32 channels hold M*CI/4 gather accumulators per
     // lane and spend long on float32 MFMAs with two waves per SIMD; there the
-    // LDS-tile kernel is faster.  bf16 rows of 64 channels still gain.
+    // tile pass is faster.  bf16 rows of 64 channels still gain.
     return reg_w_bytes<M, CI, CO, kBf>() <= 131072 && CI % 16 == 0 &&
            (CI <= 32 || (kBf && CI <= 64)) && CO % 16 == 0 && (!kBf || (CI / 4) % 8 == 0);
 }
@@ -1848,7 +1802,7 @@ __global__ void __launch_bounds__((kWsGather + kWsMma) * 64, 1)
                                                        Ds[buf], SD, w * RPW, stage[w], inv_tau,
                                                        pipe);
         } else {
-            ahead = gather_rows<M, CO, kBasis, kBf, kBf, true, RPW, true>(
+            ahead = gather_rows<M, CO, kBasis, kBf, kBf, true, RPW>(
                 wave_rows(s), n_in, col_ptr, row_idx, perm, v, g, dY, Ds[buf], SD, w * RPW,
                 stage[w], inv_r, inv_tau, ahead, wave_rows(s + 1));
         }
@@ -2265,14 +2219,10 @@ bool fused_backward_available(int32_t M, int32_t CI, int32_t CO, bool bf) {
     return find_bwd(Shape{M, CI, CO, bf}, 0) != nullptr;
 }
 
-// Workspace of the fused kernels: a permuted copy of W, the per-block dW
-// partials, the packed event coordinates, and for M = 10 (the weighted basis,
-// whose values need whole rows) the materialised basis values.
-size_t fused_workspace_bytes(int32_t M, int32_t CI, int32_t CO, int32_t n_points, int64_t nnz) {
-    return align_up((size_t)M * CI * CO * 4) +
-           align_up((size_t)kMaxBlocksBwd * (size_t)CI * M * CO * 4) +
-           align_up((size_t)(n_points > 0 ? n_points : 0) * sizeof(int4)) +
-           (M == 10 ? align_up((size_t)(nnz > 0 ? nnz : 0) * M * 4) : 0);
+// Workspace of the backward: the per-block dW partials and the packed events.
+size_t fused_workspace_bytes(int32_t M, int32_t CI, int32_t CO, int32_t n_points) {
+    return align_up((size_t)kMaxBlocksBwd * (size_t)CI * M * CO * 4) +
+           align_up((size_t)(n_points > 0 ? n_points : 0) * sizeof(int4));
 }
 
 // The forward: the packed events and the row order.
@@ -2401,7 +2351,7 @@ sbc_status fused_backward(const sbc_csr *csr, const sbc_csc *csc, const float *v
     if (!fn) return fail(SBC_ERR_UNSUPPORTED, "no fused backward for this shape");
     const int32_t n_in = csr->n_cols;
     char *base = static_cast<char *>(ws);
-    float *part = reinterpret_cast<float *>(base + align_up((size_t)M * CI * CO * 4));
+    float *part = reinterpret_cast<float *>(base);
     // the kernel reads W [M, CI, CO] in place as Wt [CI, M*CO]
     const WsCfg cfg = ws_cfg_rt(M, CI, CO, bf);
     const int TR = mode == SBC_BASIS_EVENT8 + 1 && M == 8 && CI == 32 && CO == 32 && !bf
@@ -2414,10 +2364,8 @@ sbc_status fused_backward(const sbc_csr *csr, const sbc_csc *csc, const float *v
     if (blocks > n_tiles) blocks = n_tiles;
     if (blocks < 1) blocks = 1;
     KGeo gg;
-    // layout: [W copy][dW partials][packed events]
-    SBC_TRY(make_kgeo(csr, v, g,
-                      base + align_up((size_t)M * CI * CO * 4) +
-                          align_up((size_t)kMaxBlocksBwd * (size_t)CI * M * CO * 4),
+    // layout: [dW partials][packed events]
+    SBC_TRY(make_kgeo(csr, v, g, base + align_up((size_t)kMaxBlocksBwd * (size_t)CI * M * CO * 4),
                       stream, &gg));
     if (n_in > 0 && (dF || dW)) {
         trace_before(decay_derivative ? "decay_fused" : "bwd_fused", stream);

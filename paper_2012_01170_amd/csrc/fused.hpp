@@ -16,7 +16,7 @@ constexpr int kMaxBlocksBwd = 256;
 bool fused_forward_available(int32_t M, int32_t CI, int32_t CO, bool bf);
 bool fused_backward_available(int32_t M, int32_t CI, int32_t CO, bool bf);
 // n_points: the larger of the input and output counts
-size_t fused_workspace_bytes(int32_t M, int32_t CI, int32_t CO, int32_t n_points, int64_t nnz);
+size_t fused_workspace_bytes(int32_t M, int32_t CI, int32_t CO, int32_t n_points);
 // the forward's
 size_t fused_forward_workspace_bytes(int32_t n_points);
 
