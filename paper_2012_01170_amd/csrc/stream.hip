@@ -135,6 +135,12 @@ __global__ void __launch_bounds__(kStreamThreads)
 // 796 us by the lists, 343 us here; four rates a pixel, batches of 7639 (12 to
 // 12): 641 and 386.  The comparisons grow with n^2, so longer batches (12766:
 // equal times by then) stay on the lists.
+// On few hot pixels the walks are long chains of dependent loads that also skip
+// the later events, where the lists read consecutive entries; with one rate or two
+// they are still the faster ones (four batches of 4096 events on 4 pixels, 16
+// channels: 4871 -> 3180 us and 5000 -> 4416), with four rates on 4 to 16 pixels
+// they are not (5742 -> 7098, 1711 -> 1908).  The host does not see the pixels,
+// and the same shape is faster on ordinary streams, so no rule says otherwise.
 //   1. links: an event's predecessor in its pixel is the latest earlier event
 //      with its key, found by comparing keys with every event of the batch
 //      (16.8 M compares for 4096); an event with no later
@@ -393,7 +399,8 @@ __global__ void __launch_bounds__(kStreamThreads)
 }
 
 // LDS of the short batches' output kernel, and whether a batch takes that path:
-// its links fit in LDS, and so do 16 rows of G.
+// its links fit in LDS, and so do 16 rows of G (64 KB: two blocks a CU; wider
+// rows, four rates of 28 channels or one of 112, stay on the lists).
 size_t short_lds(int32_t K) {
     return ((size_t)kShortRows * short_stride(K) + (size_t)kShortThreads * 4) * 4;
 }
