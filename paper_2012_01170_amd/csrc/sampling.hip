@@ -26,12 +26,24 @@ namespace {
 
 constexpr int kSampMax = 8192;  // points per cloud held in LDS
 // Clouds of up to kSampNear points keep their coordinates and row bounds in
-// LDS too, and their neighbours while the cloud has at most kSampEdges edges:
-// a farthest-point step is a chain (argmax, the chosen point's row, its
-// neighbours, their coordinates, the distances), and each link from memory
-// costs several times what it costs from LDS.
+// LDS too, and their neighbours where they fit: a farthest-point step is a chain
+// (argmax, the chosen point's row, its neighbours, their coordinates, the
+// distances), and each link from memory costs several times what it costs from
+// LDS.
 constexpr int kSampNear = 2048;
-constexpr int kSampEdges = 24576;
+constexpr int kCus = 256;  // of an MI355X
+// That stage's bytes by the blocks that are to share a CU (160 KB beside 41 KB a
+// block of words and states): one takes 2048 points and 24576 neighbours, which
+// leaves no room for a second block.  A chain of dependent steps leaves a CU
+// idle most of the time, so blocks side by side cost each other little, and with
+// more clouds than CUs a stage that keeps them apart costs a whole turn.  Quarter
+// of the points by the farthest of all, us with no stage / the full stage for any
+// number of clouds / this rule: 256 clouds of 256 points 104 / 51 / 51, 300 of
+// them 107 / 90 / 53, 1024 of them 201 / 172 / 98, 512 of 1024 points 471 / 354 /
+// 196, 768 of 2048 1243 / 1382 / 933.
+__host__ __device__ constexpr int samp_stage_bytes(int per_cu) {
+    return per_cu == 1 ? 16 * kSampNear + 16 + 2 * 24576 : per_cu == 2 ? 40448 : 13056;
+}
 
 // the canonical form, with no contraction of the products into the sums
 __device__ __forceinline__ float sq_dist(const float3 &a, const float3 &b) {
@@ -67,6 +79,7 @@ struct SampleArgs {
     const int32_t *splits;
     const int32_t *row_ptr, *col_idx;  // in-place ball CSR (may be null for exact IFP)
     int32_t method, per_cloud;
+    int32_t near_cap;                  // clouds of at most this many points take the stage
     const int32_t *out_splits;         // (null in the counting pass of rejection sampling)
     int32_t *out_idx, *counts;
     float *dmin2;
@@ -76,19 +89,28 @@ struct SampleArgs {
 // sampling alone decides its points here to count them); kWrite true: the
 // sampling, writing the indices at out_splits[b] and the squared distances.
 // T threads: a step scans n / T distances a thread and meets T / 64 waves.
-template <bool kWrite, int T>
-__global__ void __launch_bounds__(T) sample_kernel(SampleArgs A) {
-    __shared__ float s_d[kSampMax];
+// kPerCu: the blocks a CU is to hold.
+template <bool kWrite, int T, int kPerCu>
+__global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kPerCu * T / 256 < 4 ? kPerCu * T / 256 : 4)))
+    sample_kernel(SampleArgs A) {
+    constexpr int kStage = samp_stage_bytes(kPerCu);
+    // a point's squared distance (its bits), later with the sign for "taken"
     __shared__ __attribute__((aligned(16))) int32_t s_word[kSampMax];
     __shared__ uint8_t s_st[kSampMax];  // 0 undecided, 1 taken, 2 rejected
-    __shared__ float3 s_x[kSampNear];
-    __shared__ int32_t s_ptr[kSampNear + 1];
-    __shared__ uint16_t s_col[kSampEdges];
+    // [near_cap] coordinates, [near_cap + 1] row bounds, neighbours in the rest
+    __shared__ __attribute__((aligned(16))) char s_stage[kStage];
     __shared__ __attribute__((aligned(16))) int64_t s_best[2][T / 64];
     __shared__ int32_t s_count[T / 64];
     __shared__ int32_t s_cnt;
     constexpr int kWaves = T / 64;
+    static_assert(sizeof(s_word) + sizeof(s_st) + kStage + sizeof(s_best) + sizeof(s_count) + 16 <=
+                      163840 / kPerCu,
+                  "LDS of a CU");
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    float3 *const s_x = reinterpret_cast<float3 *>(s_stage);
+    int32_t *const s_ptr = reinterpret_cast<int32_t *>(s_stage + 12 * A.near_cap);
+    uint16_t *const s_col = reinterpret_cast<uint16_t *>(s_stage + 16 * A.near_cap + 4);
+    const int32_t edge_cap = (kStage - 16 * A.near_cap - 4) / 2;
     const int32_t b = blockIdx.x;
     const int32_t s = A.splits[b], n = A.splits[b + 1] - s;
     const bool rej = A.method == SBC_SAMPLE_REJECTION || A.method == SBC_SAMPLE_APPROX_IFP_REJECTION;
@@ -101,14 +123,16 @@ __global__ void __launch_bounds__(T) sample_kernel(SampleArgs A) {
         if (tid == 0) A.counts[b] = A.per_cloud < n ? A.per_cloud : n;
         return;
     }
-    const bool near = n <= kSampNear;
+    const bool near = n <= A.near_cap;
     int32_t e_first = 0;
     bool cols = false;  // the cloud's neighbours are in s_col
+    int32_t e_last = 0;
     if (near) {
         if (approx && n > 0) {
             e_first = A.row_ptr[s];
             const int32_t e_end = A.row_ptr[s + n];
-            cols = e_end >= e_first && e_end - e_first <= kSampEdges;
+            cols = e_end >= e_first && e_end - e_first <= edge_cap;
+            e_last = e_end - e_first;
             if (cols)
                 for (int32_t e = tid; e < e_end - e_first; e += T) {
                     // (a neighbour outside the cloud is marked: it never counts)
@@ -128,73 +152,82 @@ __global__ void __launch_bounds__(T) sample_kernel(SampleArgs A) {
         const float *p = A.x + 3 * ((int64_t)s + j);
         return make_float3(p[0], p[1], p[2]);
     };
-    // row j's entries, and the neighbour of one (negative: outside the cloud).
-    // (Bounds that do not ascend belong to no ball pattern: in LDS they are kept
-    // inside the staged entries.)
-    auto row = [&](int32_t j, int32_t &e0, int32_t &e1) {
-        if (cols) {
-            const int32_t last = s_ptr[n];
-            e0 = s_ptr[j] > 0 ? s_ptr[j] : 0;
-            e1 = s_ptr[j + 1] < last ? s_ptr[j + 1] : last;
-        } else {
-            e0 = A.row_ptr[s + j];
-            e1 = A.row_ptr[s + j + 1];
-        }
+    // Row j's entries, the neighbour of one (negative: outside the cloud) and a
+    // point, from LDS and from memory.  (Bounds that do not ascend belong to no
+    // ball pattern: in LDS they are kept inside the staged entries.)
+    auto lds_point = [&](int32_t j) { return s_x[j]; };
+    auto mem_point = [&](int32_t j) {
+        const float *p = A.x + 3 * ((int64_t)s + j);
+        return make_float3(p[0], p[1], p[2]);
     };
-    auto neighbour = [&](int32_t e) {
-        if (cols) {
-            const uint16_t k = s_col[e];
-            return k == 0xFFFF ? -1 : (int32_t)k;
-        }
+    auto lds_row = [&](int32_t j, int32_t &e0, int32_t &e1) {
+        e0 = s_ptr[j] > 0 ? s_ptr[j] : 0;
+        e1 = s_ptr[j + 1] < e_last ? s_ptr[j + 1] : e_last;
+    };
+    auto mem_row = [&](int32_t j, int32_t &e0, int32_t &e1) {
+        e0 = A.row_ptr[s + j];
+        e1 = A.row_ptr[s + j + 1];
+    };
+    auto lds_entry = [&](int32_t e) {
+        const uint16_t k = s_col[e];
+        return k == 0xFFFF ? -1 : (int32_t)k;
+    };
+    auto mem_entry = [&](int32_t e) {
         const int32_t k = A.col_idx[e] - s;
         return k < n ? k : -1;
     };
     for (int32_t j = tid; j < n; j += T) {
-        s_d[j] = INFINITY;
+        s_word[j] = __float_as_int(INFINITY);
         s_st[j] = 0;
     }
     if (tid == 0) s_cnt = 0;
     __syncthreads();
     if (rej) {
-        // rounds of the first maximal independent set of the ball graph
-        bool more = true;
-        while (more) {
-            bool undecided = false;
+        // (where rows and neighbours come from is chosen outside the loops)
+        auto decide = [&](auto coords, auto bounds, auto entry) {
+            // rounds of the first maximal independent set of the ball graph
+            bool more = true;
+            while (more) {
+                bool undecided = false;
+                for (int32_t j = tid; j < n; j += T) {
+                    if (s_st[j] != 0) continue;
+                    bool pending = false, hit = false;
+                    int32_t e, e1;
+                    bounds(j, e, e1);
+                    for (; e < e1; ++e) {
+                        const int32_t k = entry(e);
+                        if (k < 0 || k >= j) continue;  // later points (and any outside the cloud)
+                        const uint8_t st = s_st[k];
+                        if (st == 1) { hit = true; break; }
+                        if (st == 0) pending = true;
+                    }
+                    if (hit) s_st[j] = 2;
+                    else if (!pending) s_st[j] = 1;
+                    else undecided = true;
+                }
+                more = __syncthreads_or(undecided);
+            }
+            // distances to the nearest taken neighbour; count the taken points
+            int32_t mine = 0;
             for (int32_t j = tid; j < n; j += T) {
-                if (s_st[j] != 0) continue;
-                bool pending = false, hit = false;
+                float d = INFINITY;
+                const float3 pj = coords(j);
                 int32_t e, e1;
-                row(j, e, e1);
+                bounds(j, e, e1);
                 for (; e < e1; ++e) {
-                    const int32_t k = neighbour(e);
-                    if (k < 0 || k >= j) continue;  // later points (and any outside the cloud)
-                    const uint8_t st = s_st[k];
-                    if (st == 1) { hit = true; break; }
-                    if (st == 0) pending = true;
+                    const int32_t k = entry(e);
+                    if (k >= 0 && s_st[k] == 1) {
+                        const float q = sq_dist(coords(k), pj);
+                        d = q < d ? q : d;
+                    }
                 }
-                if (hit) s_st[j] = 2;
-                else if (!pending) s_st[j] = 1;
-                else undecided = true;
+                s_word[j] = __float_as_int(d);
+                mine += s_st[j] == 1 ? 1 : 0;
             }
-            more = __syncthreads_or(undecided);
-        }
-        // distances to the nearest taken neighbour; count the taken points
-        int32_t mine = 0;
-        for (int32_t j = tid; j < n; j += T) {
-            float d = INFINITY;
-            const float3 pj = point(j);
-            int32_t e, e1;
-            row(j, e, e1);
-            for (; e < e1; ++e) {
-                const int32_t k = neighbour(e);
-                if (k >= 0 && s_st[k] == 1) {
-                    const float q = sq_dist(point(k), pj);
-                    d = q < d ? q : d;
-                }
-            }
-            s_d[j] = d;
-            mine += s_st[j] == 1 ? 1 : 0;
-        }
+            return mine;
+        };
+        const int32_t mine = cols ? decide(lds_point, lds_row, lds_entry)
+                                  : decide(mem_point, mem_row, mem_entry);
         atomicAdd(&s_cnt, mine);  // an integer count: order-free
         __syncthreads();
     }
@@ -237,8 +270,7 @@ __global__ void __launch_bounds__(T) sample_kernel(SampleArgs A) {
     int32_t bk = -1, bi = 0;
     const int32_t n4 = (n + 3) / 4;
     for (int32_t j = tid; j < 4 * n4; j += T)
-        s_word[j] = j < n ? (int32_t)(__float_as_uint(s_d[j]) | (s_st[j] == 1 ? 0x80000000u : 0u))
-                          : INT32_MIN;
+        s_word[j] = j >= n ? INT32_MIN : s_st[j] == 1 ? s_word[j] | INT32_MIN : s_word[j];
     __syncthreads();
     auto offer = [&](int32_t j, int32_t v) {
         if (v > bk) {
@@ -349,28 +381,6 @@ __global__ void __launch_bounds__(T) sample_kernel(SampleArgs A) {
         for (int q = 0; q < NP; ++q)
             if (tid + q * T < n) s_word[tid + q * T] = v[q];
     };
-    auto lds_point = [&](int32_t j) { return s_x[j]; };
-    auto mem_point = [&](int32_t j) {
-        const float *p = A.x + 3 * ((int64_t)s + j);
-        return make_float3(p[0], p[1], p[2]);
-    };
-    const int32_t e_last = cols ? s_ptr[n] : 0;
-    auto lds_row = [&](int32_t j, int32_t &e0, int32_t &e1) {
-        e0 = s_ptr[j] > 0 ? s_ptr[j] : 0;
-        e1 = s_ptr[j + 1] < e_last ? s_ptr[j + 1] : e_last;
-    };
-    auto mem_row = [&](int32_t j, int32_t &e0, int32_t &e1) {
-        e0 = A.row_ptr[s + j];
-        e1 = A.row_ptr[s + j + 1];
-    };
-    auto lds_entry = [&](int32_t e) {
-        const uint16_t k = s_col[e];
-        return k == 0xFFFF ? -1 : (int32_t)k;
-    };
-    auto mem_entry = [&](int32_t e) {
-        const int32_t k = A.col_idx[e] - s;
-        return k < n ? k : -1;
-    };
     if (!approx) {
         if (n <= 4 * T) all_steps(std::integral_constant<int, 4>{});
         else if (n <= 8 * T) all_steps(std::integral_constant<int, 8>{});
@@ -440,15 +450,36 @@ extern "C" sbc_status sbc_sample_points(const float *x, const int32_t *splits, i
     A.dmin2 = nullptr;
     // counts per cloud (rejection sampling runs once here to count), bounds,
     // then the sampling with its writes
-    // 256 threads where no cloud has more than kSampNear points (a step's scan is
-    // then at most 8 distances a thread), else 512
-    const bool small = max_cloud <= kSampNear;
+    // A CU is to hold as many blocks as the clouds give each, and three at most, as
+    // many as held the words and states of 8192 points alone before there was a
+    // stage.  A farthest-point step is a chain: 256 threads where no cloud has more
+    // than kSampNear points (a step's scan is then at most 8 distances a thread),
+    // else 512.  Rejection's rounds are parallel: 512 threads, and nothing staged
+    // where no steps follow or the largest cloud does not fit the stage (rejection
+    // alone, 32 clouds of 1024: 86 us with no stage, 115 staged, 78 now; 768 of 6000
+    // with it and steps, 228 and 304: the registers hold two blocks a CU).
+    const int per_cu = n_batch <= kCus ? 1 : n_batch <= 2 * kCus ? 2 : 3;
+    const int32_t fits = (samp_stage_bytes(per_cu) - 4) / 16;
+    const int32_t lim = fits < kSampNear ? fits : kSampNear;
+    const bool rounds = method == SBC_SAMPLE_REJECTION ||
+                        (method == SBC_SAMPLE_APPROX_IFP_REJECTION && max_cloud > lim);
+    const bool small = max_cloud <= kSampNear && !rounds;
+    // (max_cloud bounds no access: larger clouds are read from memory)
+    A.near_cap = method == SBC_SAMPLE_REJECTION ? 0 : max_cloud < lim ? max_cloud : lim;
     auto launch = [&](auto write) {
         constexpr bool kW = decltype(write)::value;
-        if (small)
-            hipLaunchKernelGGL((sample_kernel<kW, 256>), dim3(n_batch), dim3(256), 0, stream, A);
-        else
-            hipLaunchKernelGGL((sample_kernel<kW, 512>), dim3(n_batch), dim3(512), 0, stream, A);
+        auto with = [&](auto per) {
+            constexpr int P = decltype(per)::value;
+            if (small)
+                hipLaunchKernelGGL((sample_kernel<kW, 256, P>), dim3(n_batch), dim3(256), 0,
+                                   stream, A);
+            else
+                hipLaunchKernelGGL((sample_kernel<kW, 512, P>), dim3(n_batch), dim3(512), 0,
+                                   stream, A);
+        };
+        if (per_cu == 1) with(std::integral_constant<int, 1>{});
+        else if (per_cu == 2) with(std::integral_constant<int, 2>{});
+        else with(std::integral_constant<int, 3>{});
     };
     trace_before("sample_count", stream);
     launch(std::false_type{});

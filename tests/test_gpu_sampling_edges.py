@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 def _cloud(seed, sizes):
     rng = np.random.default_rng(seed)
     x = np.concatenate([workloads.ellipsoid_surface_points(rng, n, rng.uniform(0.5, 1.0, size=3))
-                        for n in sizes])
+                        for n in sizes if n])
     return x, np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
 
 
@@ -79,3 +79,31 @@ def test_featureless_block_edges(n, P, basis):
     dPhi = G.sbc.featureless_backward(csr, t["dY"], w["M"], geometry=geo).cpu().numpy()
     assert G.norm_error(Z, oracle.conv.featureless_forward(rp, ci, v, Phi)[0]) < G.TOL_F32
     assert G.norm_error(dPhi, oracle.conv.featureless_backward(rp, ci, v, w["dY"])) < G.TOL_F32
+
+
+# batches of more clouds than CUs share them two and three blocks each, with less
+# LDS a block for coordinates, rows and neighbours: clouds inside and beyond it
+@pytest.mark.parametrize("n_batch", [256, 257, 513])
+@pytest.mark.parametrize("method", ["ifp", "approx_ifp", "approx_ifp_rejection", "rejection"])
+def test_sampling_many_clouds(n_batch, method):
+    print(f"[sampling many] {n_batch} {method}", flush=True)
+    sizes = [1 + (7 * i) % 23 for i in range(n_batch)]
+    sizes[3], sizes[100], sizes[-1] = 830, 0, 1100
+    x, splits = _cloud(90 + n_batch, sizes)
+    rp, ci = oracle.points_csr(x, splits, x, splits, 0.2, 0)
+    xd, sd = G.dev(x), G.dev(splits)
+    ball = G.sbc.neighbour_search_points(xd, sd, xd, sd, 0.2, 0)
+    counts = [min(40, n) for n in sizes]
+    idx, osp, d2 = G.sbc.sample_points(xd, sd, method, 40, ball=ball, with_dmin=True)
+    if method == "ifp":
+        ref, dref = oracle.sampling.ifp(x, splits, counts)
+    elif method == "approx_ifp":
+        ref, dref = oracle.sampling.approx_ifp(x, splits, counts, rp, ci)
+    elif method == "approx_ifp_rejection":
+        ref, dref = oracle.sampling.approx_ifp_after_rejection(x, splits, 40, rp, ci)
+    else:
+        taken, dref = oracle.sampling.rejection_sampling(x, splits, rp, ci)
+        ref = np.nonzero(taken)[0].astype(np.int32)
+    assert int(osp[-1]) == len(ref)
+    assert np.array_equal(idx.cpu().numpy()[:len(ref)], ref)
+    assert np.array_equal(d2.cpu().numpy()[:len(x)], dref)
