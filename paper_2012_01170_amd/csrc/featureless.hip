@@ -9,7 +9,7 @@
 // on scheduling; the group then writes Z[i, :] = G~[i, :] Phi_0, a lane per
 // output channel.  Backward: dPhi_0 = G~^T dZ; a block makes G~ of kDRows rows
 // at a time in LDS and keeps its part of the product in registers, and the
-// blocks' parts are added in order (G~ never reaches memory).
+// blocks' parts are added in order (G~ reaches memory only where dZ is wide).
 #include <type_traits>
 
 #include "basis.hpp"
@@ -41,6 +41,8 @@ __device__ __forceinline__ double row16_sum(double x) {
 #undef SBC_STEP
     return x;
 }
+
+constexpr int kSumsGiven = -1;  // (a mode of the product alone, below)
 
 // G~[r, :] in every lane of the row's group (sl: the lane in it).
 // kMode: 0 basis values read from v; 1 windowed point monomials; 2 event
@@ -112,7 +114,8 @@ __device__ __forceinline__ void row_sums(int64_t r, int sl, const int32_t *__res
     }
 }
 
-template <int M, int kMode>
+// Z = G~ Phi_0, or (not kWritesZ) G~ itself, [n_rows, M].
+template <int M, int kMode, bool kWritesZ>
 __global__ void __launch_bounds__(kFThreads)
     featureless_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
                        const int32_t *__restrict__ col_idx, int64_t nnz_bound,
@@ -123,6 +126,16 @@ __global__ void __launch_bounds__(kFThreads)
     if (r >= n_rows) return;  // a group leaves as a whole
     double acc[M];
     row_sums<M, kMode>(r, sl, row_ptr, col_idx, nnz_bound, v, g, acc);
+    if constexpr (!kWritesZ) {
+        if (sl < M) {
+            float x = 0.f;
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                if (m == sl) x = (float)acc[m];
+            out[r * M + sl] = x;
+        }
+        return;
+    }
     for (int32_t p = sl; p < P; p += kFLanes) {
         double z = 0.0;
 #pragma unroll
@@ -131,8 +144,8 @@ __global__ void __launch_bounds__(kFThreads)
     }
 }
 
-// Rows of G~ a block makes at a time, and the columns of dZ its threads take at
-// a time (blockIdx.y: which kDCols).
+// Rows of G~ a block makes at a time, and the columns of dZ a row of its threads
+// takes (blockIdx.y: which NC kDCols).
 constexpr int kDRows = 64;
 constexpr int kDCols = 64;
 constexpr int kDBlocks = 512;  // partial products: two blocks per CU
@@ -140,24 +153,31 @@ constexpr int kDBlocks = 512;  // partial products: two blocks per CU
 // part[x][m, p] = sum over the block's rows r of G~[r, m] dZ[r, p].  Thread
 // (column p of kDCols, row group q of 4) sums the rows r = q mod 4 in float64;
 // the groups are added in order.  Where there are at most 32 columns a row of
-// threads is 32 wide and there are 8 groups.
-template <int M, int kMode>
+// threads is 32 wide and there are 8 groups.  NC: columns a thread takes, kDCols
+// apart.  kMode kSumsGiven: the row sums are read from v [n_rows, M].
+template <int M, int kMode, int NC>
 __global__ void __launch_bounds__(kFThreads)
     featureless_dphi_kernel(int32_t n_rows, const int32_t *__restrict__ row_ptr,
                             const int32_t *__restrict__ col_idx, int64_t nnz_bound,
                             const float *__restrict__ v, sbc_geometry g,
                             const float *__restrict__ dZ, int32_t P, float *__restrict__ part) {
-    __shared__ float G[kDRows][M];
+    __shared__ double G[kDRows][M];  // (float32 values)
     __shared__ double sums[kFThreads];
     const int tid = threadIdx.x, sl = tid % kFLanes;
-    const int32_t p0 = blockIdx.y * kDCols;
+    const int32_t p0 = blockIdx.y * (NC * kDCols);
     const int width = P - p0 <= 32 ? 32 : 64;
     const int32_t p = p0 + tid % width;
     const int q = tid / width, groups = kFThreads / width;
-    double acc[M];
+    double acc[NC][M];
 #pragma unroll
-    for (int m = 0; m < M; ++m) acc[m] = 0.0;
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int m = 0; m < M; ++m) acc[c][m] = 0.0;
     for (int64_t r0 = (int64_t)blockIdx.x * kDRows; r0 < n_rows; r0 += (int64_t)gridDim.x * kDRows) {
+        if constexpr (kMode == kSumsGiven) {
+            for (int x = tid; x < kDRows * M; x += kFThreads)
+                (&G[0][0])[x] = r0 + x / M < n_rows ? (double)v[r0 * M + x] : 0.0;
+        } else
 #pragma unroll 1
         for (int i = tid / kFLanes; i < kDRows; i += kFThreads / kFLanes) {
             double s[M];
@@ -168,32 +188,48 @@ __global__ void __launch_bounds__(kFThreads)
 #pragma unroll
                 for (int m = 0; m < M; ++m)
                     if (m == sl) x = on ? (float)s[m] : 0.f;
-                G[i][sl] = x;
+                G[i][sl] = (double)x;
             }
         }
         __syncthreads();
         if (p < P) {
             const int64_t left = n_rows - r0;
             const int rows = left < kDRows ? (int)left : kDRows;
-            for (int i = q; i < rows; i += groups) {
-                const double z = (double)dZ[(r0 + i) * P + p];
+            // 4 rows' loads in flight (rows past the last: G is 0 there)
+            static_assert(kDRows % (4 * 8) == 0, "whole steps");
+            for (int i = q; i < rows; i += 4 * groups) {
+                float z[4][NC];
 #pragma unroll
-                for (int m = 0; m < M; ++m) acc[m] += (double)G[i][m] * z;
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        z[u][c] = i + u * groups < rows && p + c * kDCols < P
+                                      ? dZ[(r0 + i + u * groups) * P + p + c * kDCols]
+                                      : 0.f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int m = 0; m < M; ++m)
+                            acc[c][m] += G[i + u * groups][m] * (double)z[u][c];
             }
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-        sums[tid] = acc[m];
-        __syncthreads();
-        if (q == 0 && p < P) {
-            double t = 0.0;
-            for (int k = 0; k < groups; ++k) t += sums[k * width + tid];
-            part[((int64_t)blockIdx.x * M + m) * P + p] = (float)t;
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            sums[tid] = acc[c][m];
+            __syncthreads();
+            if (q == 0 && p + c * kDCols < P) {
+                double t = 0.0;
+                for (int k = 0; k < groups; ++k) t += sums[k * width + tid];
+                part[((int64_t)blockIdx.x * M + m) * P + p + c * kDCols] = (float)t;
+            }
+            __syncthreads();
         }
-        __syncthreads();
-    }
 }
 
 // dPhi[x] = sum over blocks of part[block][x], in block order within 16 groups
@@ -229,6 +265,14 @@ int32_t dphi_blocks(int32_t n) {
     const int32_t b = (n + kDRows - 1) / kDRows;
     return b < kDBlocks ? b : kDBlocks;
 }
+
+// Up to this many columns the blocks make the row sums as they go, for every 64
+// columns again; beyond it a pass of its own makes them once, and a thread takes
+// two columns.  32768 rows, M 8, 20 entries: 128 columns 26 us by the first way,
+// 256 columns 45 and 34 us, 1024 columns 121 and 81.  What is left against a float32
+// matrix product of the stored sums (37 and 74 us) are the float64 sums, which
+// are kept; four columns a thread took 108 (registers).
+constexpr int kSumsColumns = 128;
 
 // f(M, mode) for the basis of a call
 template <typename F>
@@ -274,7 +318,8 @@ using namespace sbc;
 
 extern "C" size_t sbc_featureless_workspace_size(int32_t n_out, int32_t M, int32_t P) {
     if (n_out < 0 || M <= 0 || P <= 0) return 0;
-    return align_up((size_t)dphi_blocks(n_out) * M * P * 4);
+    return align_up((size_t)dphi_blocks(n_out) * M * P * 4) +
+           (P > kSumsColumns ? align_up((size_t)n_out * M * 4) : 0);
 }
 
 extern "C" sbc_status sbc_featureless_forward(const sbc_csr *csr, const float *v,
@@ -288,7 +333,7 @@ extern "C" sbc_status sbc_featureless_forward(const sbc_csr *csr, const float *v
     trace_before("featureless_fwd", stream);
     const sbc_geometry g = geometry ? *geometry : sbc_geometry{};
     featureless_dispatch(v, geometry, M, [&](auto m, auto mode) {
-        hipLaunchKernelGGL((featureless_kernel<decltype(m)::value, decltype(mode)::value>),
+        hipLaunchKernelGGL((featureless_kernel<decltype(m)::value, decltype(mode)::value, true>),
                            dim3(grid_for((int64_t)csr->n_rows * kFLanes, kFThreads)),
                            dim3(kFThreads), 0, stream, csr->n_rows, csr->row_ptr, csr->col_idx,
                            csr->nnz_bound, v, g, Phi, P, Z);
@@ -315,12 +360,26 @@ extern "C" sbc_status sbc_featureless_backward(const sbc_csr *csr, const float *
     float *part = static_cast<float *>(workspace);
     const sbc_geometry g = geometry ? *geometry : sbc_geometry{};
     const int32_t blocks = dphi_blocks(n);
+    float *sums = reinterpret_cast<float *>(static_cast<char *>(workspace) +
+                                            align_up((size_t)blocks * M * P * 4));
     trace_before("featureless_rowsum", stream);
     featureless_dispatch(v, geometry, M, [&](auto m, auto mode) {
-        hipLaunchKernelGGL((featureless_dphi_kernel<decltype(m)::value, decltype(mode)::value>),
-                           dim3((unsigned)blocks, (unsigned)((P + kDCols - 1) / kDCols)),
-                           dim3(kFThreads), 0, stream, n, csr->row_ptr, csr->col_idx,
-                           csr->nnz_bound, v, g, dZ, P, part);
+        constexpr int kM = decltype(m)::value, kMode = decltype(mode)::value;
+        auto product = [&](auto kernel, int columns, const float *vals) {
+            hipLaunchKernelGGL(kernel,
+                               dim3((unsigned)blocks, (unsigned)((P + columns - 1) / columns)),
+                               dim3(kFThreads), 0, stream, n, csr->row_ptr, csr->col_idx,
+                               csr->nnz_bound, vals, g, dZ, P, part);
+        };
+        if (P <= kSumsColumns) {
+            product(featureless_dphi_kernel<kM, kMode, 1>, kDCols, v);
+        } else {
+            hipLaunchKernelGGL((featureless_kernel<kM, kMode, false>),
+                               dim3(grid_for((int64_t)n * kFLanes, kFThreads)), dim3(kFThreads), 0,
+                               stream, n, csr->row_ptr, csr->col_idx, csr->nnz_bound, v, g,
+                               nullptr, P, sums);
+            product(featureless_dphi_kernel<kM, kSumsGiven, 2>, 2 * kDCols, sums);
+        }
     });
     SBC_LAUNCH_CHECK();
     trace_after("featureless_rowsum", stream);

@@ -107,3 +107,10 @@ def test_sampling_many_clouds(n_batch, method):
     assert int(osp[-1]) == len(ref)
     assert np.array_equal(idx.cpu().numpy()[:len(ref)], ref)
     assert np.array_equal(d2.cpu().numpy()[:len(x)], dref)
+
+
+# wide dZ: the row sums made once (more than 128 columns), two and four a thread
+@pytest.mark.parametrize("n,P", [(64, 128), (65, 256), (63, 257), (1000, 300)])
+@pytest.mark.parametrize("basis", [workloads.BASIS_MONO4, workloads.BASIS_WMONO10])
+def test_featureless_wide(n, P, basis):
+    test_featureless_block_edges(n, P, basis)
