@@ -78,10 +78,8 @@ TRACE_NAME = {"bwd_ws_kernel": "bwd_fused",
               "tile_dw_kernel": "bwd_tile_dw",
               "fwd_reg_kernel": "fwd_fused", "fwd_onehot_kernel": "fwd_fused",
               "dw_reduce_kernel": "bwd_dw_reduce",
-              "sample_kernel<true>": "sample", "sample_kernel<false>": "sample_count",
-              "sample_kernel<true, 256>": "sample", "sample_kernel<true, 512>": "sample",
+              "featureless_dphi_kernel": "featureless_rowsum",
               "featureless_reduce_kernel": "featureless_dphi",
-              "sample_kernel<false, 256>": "sample_count", "sample_kernel<false, 512>": "sample_count",
               "lif_cell_kernel": "lif_cells", "lif_emit_kernel": "lif_emit",
               "lif_count_kernel": "lif_emit",
               "stream_link_kernel": "stream_lists", "stream_output_kernel": "stream_gather",
@@ -97,8 +95,10 @@ def trace_name(kernel):
     if base == "bwd_ws_kernel":  # <M, CI, CO, basis, ...>: basis 16 is the decay derivative
         args = kernel[len(base) + 1:].split(",")
         return "decay_fused" if len(args) > 3 and args[3].strip() == "16" else "bwd_fused"
-    if base == "featureless_kernel":  # <M, mode>; profiles kept from before: <M, mode, writes Z>
+    if base == "featureless_kernel":  # <M, mode, writes Z>: else the row sums
         return "featureless_rowsum" if kernel.rstrip(">").endswith("false") else "featureless_fwd"
+    if base == "sample_kernel":  # <writes, ...>
+        return "sample" if kernel.startswith("sample_kernel<true") else "sample_count"
     if base == "spmm_kernel":  # <M, contract, X type>: named by direction, see SPMM_DIRECTION
         args = kernel[len(base) + 1:].split(",")
         return "spmm_contract" if len(args) > 1 and args[1].strip() == "true" else "spmm_expand"
@@ -200,7 +200,7 @@ def summarize_traffic(fetch_dir, write_dir, probe_mb, command):
     out = [f"# HBM traffic per dispatch from rocprofv3 byte counters", f"# command: {command}",
            f"source_fingerprint: {source_fingerprint()}"]
     per = {}
-    factors = {}
+    factors, tile = {}, {}
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = [r for r in _counter_rows(d) if r["Counter_Name"] == counter]
         copies = [float(r["Counter_Value"]) for r in rows if "copyBuffer" in r["Kernel_Name"]]
@@ -210,6 +210,7 @@ def summarize_traffic(fetch_dir, write_dir, probe_mb, command):
         factors[counter] = probe_kib / probe
         out.append(f"{counter.lower()}_factor: {factors[counter]:.4f}  "
                    f"(copy probe {probe_mb} MiB; counter read {probe:.0f} KiB)")
+        tile[counter] = tile_contract_launches(rows)
         for r in rows:
             k = short_kernel_name(r["Kernel_Name"])
             per.setdefault(k, {}).setdefault(counter, []).append(float(r["Counter_Value"]))
@@ -231,7 +232,28 @@ def summarize_traffic(fetch_dir, write_dir, probe_mb, command):
         if trace_name(k):
             out.append(f"traffic {trace_name(k)} {base} {fk:.1f} {wk:.1f} {b:.0f} "
                        f"{kernel_fingerprint(base)}")
+    for name in tile["FETCH_SIZE"]:
+        fk = statistics.mean(tile["FETCH_SIZE"][name])
+        wk = statistics.mean(tile["WRITE_SIZE"][name])
+        b = (fk * factors["FETCH_SIZE"] + wk * factors["WRITE_SIZE"]) * 1024.0
+        out.append(f"traffic {name} tile_contract_kernel {fk:.1f} {wk:.1f} {b:.0f} "
+                   f"{kernel_fingerprint('tile_contract_kernel')}")
     return "\n".join(out) + "\n"
+
+
+def tile_contract_launches(rows):
+    """The readings of tile_contract_kernel by launch name: the forward, or, where
+    the step has a tile weight gradient too, the forward and the input gradient
+    in turn."""
+    names = [short_kernel_name(r["Kernel_Name"]).split("<")[0] for r in rows]
+    both = "tile_dw_kernel" in names
+    out = {}
+    for r in rows:
+        if short_kernel_name(r["Kernel_Name"]).split("<")[0] == "tile_contract_kernel":
+            seen = sum(len(v) for v in out.values())
+            name = "bwd_tile_df" if both and seen % 2 else "fwd_fused"
+            out.setdefault(name, []).append(float(r["Counter_Value"]))
+    return out
 
 
 def _counter_by_kernel(directory, counter):

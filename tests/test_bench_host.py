@@ -75,6 +75,23 @@ def test_traffic_summary_is_calibrated_by_the_copy_probe(tmp_path):
     assert line[6] == bench.kernel_fingerprint("bwd_ws_kernel")
 
 
+@pytest.mark.parametrize("both", [True, False])
+def test_traffic_of_the_tile_contraction_is_filed_by_launch(tmp_path, both):
+    """One device function serves the forward and the input gradient: with a tile
+    weight gradient in the step its dispatches are the two in turn."""
+    c = "void sbc::tile_contract_kernel<8, false, 1, true, 4, 2>(A)"
+    d = "void sbc::tile_dw_kernel<8, false, 1, 4>(A)"
+    step = [(c, 100.0), (c, 40.0), (d, 7.0)] if both else [(c, 100.0)]
+    fetch = _counter_dir(tmp_path, "fetch", "FETCH_SIZE", [("__amd_rocclr_copyBuffer", 1024.0)] + 2 * step)
+    write = _counter_dir(tmp_path, "write", "WRITE_SIZE", [("__amd_rocclr_copyBuffer", 1024.0)] + 2 * step)
+    got = {l.split()[1]: float(l.split()[5]) for l in bench.summarize_traffic(fetch, write, 1, "cmd").splitlines()
+           if l.startswith("traffic")}
+    want = {"fwd_fused": 200 * 1024.0}
+    if both:
+        want.update(bwd_tile_df=80 * 1024.0, bwd_tile_dw=14 * 1024.0)
+    assert got == pytest.approx(want)
+
+
 def test_counter_summary_averages_dispatches_and_drops_small_kernels(tmp_path):
     """Per kernel, a counter's readings are averaged over dispatches; kernels
     under 2% of the largest one's wave-cycles are left out."""
