@@ -112,7 +112,7 @@ typedef enum {
  *               [n_out, M*C_in], then one dense contraction with W.
  *   GEMM_FIRST  N^(m) (F W^(m)): one dense contraction H = F [W^(0)..W^(M-1)]
  *               [n_in, M*C_out], then gather-accumulate over H.
- *   AUTO        the library picks by the multiply-add counts of both orders.
+ *   AUTO        the library picks by the estimated cost of both (sbc_conv_plan).
  * The backward pass uses the transposed counterpart of the chosen order.
  */
 typedef enum {
@@ -559,18 +559,22 @@ const char *sbc_kernel_names(void);
  *                   evaluated inside, nothing of [rows, M*C] in memory), 0
  *                   when they run as separate kernels.
  *   backward_fused  1 when both gradients come out of one such kernel, 0 when
- *                   each has its own: one kernel per gradient with 8 to 512
- *                   channels (except under an explicit GEMM_FIRST; AUTO's
- *                   GEMM_FIRST then names the side the weight gradient sums
- *                   over), else separate gather and contraction kernels.
+ *                   each has its own: one kernel per gradient (8 to 512
+ *                   channels; AUTO's GEMM_FIRST then names the side the weight
+ *                   gradient sums over), or separate gather and contraction
+ *                   kernels.
  * AUTO picks the order with the lower estimated cost: the multiply-adds of
  * the paper's cost table, plus 5e7 multiply-adds (about 5 us, measured) for
  * every kernel launch, a fused pass counting as two launches and a pass of
  * separate gather and contraction kernels as five.  The launch term only
  * matters for small problems, where it prefers the fused pass.  Where a
- * gather-first pass of one kernel serves any channel count (8 to 512), it is
- * taken unless there are more result rows than gathered ones.  For the
- * backward the rule is applied to the transposed problem.
+ * gather-first pass of one kernel serves any channel count (8 to 512) and the
+ * shape has no fused kernel of its own, the estimated times of that pass and
+ * of the separate kernels of both orders decide (of one order where it is
+ * given; an up-sampling forward that the multiply-adds give to GEMM_FIRST stays
+ * there).  The plan is that of basis values evaluated inside; given values of 24
+ * and 32 functions are estimated higher.  For the backward the rule is applied
+ * to the transposed problem.
  */
 typedef struct {
     sbc_order forward_order;

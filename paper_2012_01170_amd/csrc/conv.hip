@@ -18,6 +18,7 @@
 #include "common.hpp"
 #include "fused.hpp"
 #include "gemm.hpp"
+#include "route_cost.hpp"
 #include "spmm.hpp"
 #include "tile.hpp"
 
@@ -82,11 +83,15 @@ sbc_status permute_w_back(const float *dwp, int32_t M, int32_t Ci, int32_t Co, f
     return SBC_OK;
 }
 
-// Routes of the four products.  Forward: SpMM-first gathers G = N F then
-// contracts with W; GEMM-first contracts H = F W then gathers over H.
-// Backward: the D-route gathers D = N^T dY first (dF = D Wt, dW = F^T D), the
-// G-route contracts dG = dY W^T first (dF = N^T dG) with dW = G^T dY.
-enum Route { kFwdSpmm, kFwdGemm, kBwdD, kBwdG };
+// Routes of the products.  Forward: SpMM-first gathers G = N F then contracts
+// with W; GEMM-first contracts H = F W then gathers over H.  Backward: the
+// D-route gathers D = N^T dY first (dF = D Wt, dW = F^T D), the G-route
+// contracts dG = dY W^T first (dF = N^T dG) with dW = G^T dY.  As tile passes
+// (tile.hpp) a forward gathers first, and so does the input gradient; the weight
+// gradient sums over the n_in rows (D) or the n_out rows (G).
+enum Route { kFwdSpmm, kFwdGemm, kBwdD, kBwdG, kFwdTile, kBwdTileD, kBwdTileG };
+
+bool route_tile(Route r) { return r >= kFwdTile; }
 
 struct ConvWs {
     float *v;        // [nnz, M] basis values (when not supplied)
@@ -128,6 +133,8 @@ ConvWs carve_route(void *base, Route r, int32_t n_out, int32_t n_in, int64_t nnz
             upd(gemm_workspace_floats(M * Ci, Co, n_out));
             upd(gemm_workspace_floats(n_out, M * Ci, Co));
             break;
+        default:  // tile passes: carve_tile()
+            break;
     }
     w.partial = cv.take<float>(p);
     if (bytes) *bytes = cv.used;
@@ -153,33 +160,24 @@ TileWs carve_tile(void *base, Route r, int32_t n_out, int32_t n_in, int32_t M, i
     Carver cv(base);
     TileWs w{};
     const int32_t n = n_out > n_in ? n_out : n_in;
-    w.frag = cv.take<char>(r == kFwdSpmm ? tile_frag_bytes(M, Ci, Co, bf)
+    w.frag = cv.take<char>(r == kFwdTile ? tile_frag_bytes(M, Ci, Co, bf)
                                          : tile_frag_bytes(M, Co, Ci, bf));
     w.packed = cv.take<int4>((size_t)(M % 8 == 0 && n > 0 ? n : 0));
     w.wsum = cv.take<double>((size_t)(M == 10 ? n_out : 0));
-    if (r == kBwdD) w.part = cv.take<char>(tile_dw_bytes(n_in, M, Ci, Co));
-    if (r == kBwdG) w.part = cv.take<char>(tile_dw_bytes(n_out, M, Co, Ci));
+    if (r == kBwdTileD) w.part = cv.take<char>(tile_dw_bytes(n_in, M, Ci, Co));
+    if (r == kBwdTileG) w.part = cv.take<char>(tile_dw_bytes(n_out, M, Co, Ci));
     if (bytes) *bytes = cv.used;
     return w;
 }
 
-// Shapes that take the tile passes where the route allows it: those without a
-// fused kernel of their own.
+// Shapes that the tile passes serve: those without a fused kernel of their own.
 bool tile_shape(Route r, int32_t M, int32_t Ci, int32_t Co, bool bf) {
     return tile_available(M, Ci, Co) && !route_fused(r, M, Ci, Co, bf);
 }
 
-// Whether a route runs as tile passes: the gather-first ones, and under AUTO
-// the G-route, whose input gradient then gathers first all the same (its
-// weight gradient still sums over the n_out rows).
-bool route_tile(Route r, int32_t M, int32_t Ci, int32_t Co, bool bf, sbc_order order) {
-    if (r == kFwdGemm || (r == kBwdG && order != SBC_ORDER_AUTO)) return false;
-    return tile_shape(r, M, Ci, Co, bf);
-}
-
 size_t route_bytes(Route r, int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t Ci,
-                   int32_t Co, bool bf, sbc_order order) {
-    if (route_tile(r, M, Ci, Co, bf, order)) {
+                   int32_t Co, bool bf) {
+    if (route_tile(r)) {
         size_t b = 0;
         carve_tile(nullptr, r, n_out, n_in, M, Ci, Co, bf, &b);
         return b;
@@ -200,12 +198,11 @@ size_t route_bytes(Route r, int32_t n_out, int32_t n_in, int64_t nnz, int32_t M,
 // pass of separate gather and contraction kernels as kSplitLaunches.  The
 // launch term only decides between orders whose multiply-adds differ by less
 // than a few launches' worth, i.e. small problems, where the fused pass wins.
-// Shapes of the tile passes gather first unless there are more result rows
-// than gathered ones: the tile pass keeps the intermediate on the CU, where
-// the separate kernels write and read M C floats a row, which costs more than
-// the multiply-adds a contraction first would save (in place, M 8, 128 -> 32
-// channels, 16 edges a row).  With more result rows (up-sampling) the
-// multiply-adds decide as for the others.
+// Shapes that the tile passes serve are decided by estimated times instead
+// (route_cost.hpp): the tile pass against the separate kernels of either order
+// (under an explicit order, of that order).  A forward with more result rows
+// than gathered ones (up-sampling) contracts first where the multiply-adds say
+// so, as the others do.
 constexpr double kLaunchMacs = 5e7;
 constexpr double kFusedLaunches = 2, kSplitLaunches = 5;
 
@@ -217,32 +214,52 @@ double order_macs(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t C
 }
 
 Route forward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t Ci, int32_t Co,
-                    sbc_order order, bool bf) {
-    if (order == SBC_ORDER_SPMM_FIRST) return kFwdSpmm;
+                    sbc_order order, bool bf, bool values) {
     if (order == SBC_ORDER_GEMM_FIRST) return kFwdGemm;
-    if (n_out <= n_in && tile_shape(kFwdSpmm, M, Ci, Co, bf)) return kFwdSpmm;
-    const double spmm = order_macs(n_out, n_in, nnz, M, Ci, Co, true) +
-                        kLaunchMacs * (route_fused(kFwdSpmm, M, Ci, Co, bf) ? kFusedLaunches
-                                                                             : kSplitLaunches);
-    const double gemm = order_macs(n_out, n_in, nnz, M, Ci, Co, false) +
-                        kLaunchMacs * kSplitLaunches;
-    return spmm <= gemm ? kFwdSpmm : kFwdGemm;
+    const double macs_spmm = order_macs(n_out, n_in, nnz, M, Ci, Co, true) +
+                             kLaunchMacs * (route_fused(kFwdSpmm, M, Ci, Co, bf) ? kFusedLaunches
+                                                                                  : kSplitLaunches);
+    const double macs_gemm = order_macs(n_out, n_in, nnz, M, Ci, Co, false) +
+                             kLaunchMacs * kSplitLaunches;
+    const bool by_macs = order == SBC_ORDER_SPMM_FIRST || macs_spmm <= macs_gemm;
+    if (tile_shape(kFwdSpmm, M, Ci, Co, bf) && (n_out <= n_in || by_macs)) {
+        const RouteSize s{n_out, nnz, M, Ci, Co};
+        const double tile = kTileFavour * tile_contract_us(s, bf, values);
+        const double spmm = split_forward_us(s);
+        const double gemm = order == SBC_ORDER_SPMM_FIRST ? spmm : gemm_first_forward_us(s, n_in);
+        if (tile <= spmm && tile <= gemm) return kFwdTile;
+        return spmm <= gemm ? kFwdSpmm : kFwdGemm;
+    }
+    return by_macs ? kFwdSpmm : kFwdGemm;
 }
 
 // The backward is itself a convolution from the outputs back to the inputs
-// (N^T, channels C_out -> C_in); AUTO applies the same estimate to it.
+// (N^T, channels C_out -> C_in); AUTO applies the same estimates to it.
 // Explicit orders name what is done first: SPMM_FIRST = D-route, GEMM_FIRST = G-route.
+// The tile passes' weight gradient sums over the inputs, or over the outputs
+// where they are fewer and the multiply-adds say so.
 Route backward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t Ci, int32_t Co,
-                     sbc_order order, bool bf) {
-    if (order == SBC_ORDER_SPMM_FIRST) return kBwdD;
+                     sbc_order order, bool bf, bool values) {
     if (order == SBC_ORDER_GEMM_FIRST) return kBwdG;
-    if (n_in <= n_out && tile_shape(kBwdD, M, Ci, Co, bf)) return kBwdD;
     const double d = order_macs(n_in, n_out, nnz, M, Co, Ci, true) +
                      kLaunchMacs * (route_fused(kBwdD, M, Ci, Co, bf) ? kFusedLaunches
                                                                        : kSplitLaunches);
     const double g = order_macs(n_in, n_out, nnz, M, Co, Ci, false) +
                      kLaunchMacs * kSplitLaunches;
-    return d <= g ? kBwdD : kBwdG;
+    if (tile_shape(kBwdD, M, Ci, Co, bf)) {
+        const bool over_in = order == SBC_ORDER_SPMM_FIRST || n_in <= n_out || d <= g;
+        const double tile =
+            kTileFavour *
+            (tile_contract_us(RouteSize{n_in, nnz, M, Co, Ci}, bf, values) +
+             tile_dw_us(over_in ? RouteSize{n_in, nnz, M, Ci, Co} : RouteSize{n_out, nnz, M, Co, Ci},
+                        bf, values));
+        const double sd = split_d_us(n_in, nnz, M, Ci, Co);
+        const double sg = split_g_us(n_out, nnz, M, Ci, Co);
+        const bool d_first = order == SBC_ORDER_SPMM_FIRST || sd <= sg;
+        if (tile <= (d_first ? sd : sg)) return over_in ? kBwdTileD : kBwdTileG;
+        return d_first ? kBwdD : kBwdG;
+    }
+    return order == SBC_ORDER_SPMM_FIRST || d <= g ? kBwdD : kBwdG;
 }
 
 // feature, weight and gradient rows are moved 16 bytes at a time
@@ -297,14 +314,12 @@ extern "C" sbc_status sbc_conv_plan(int32_t n_out, int32_t n_in, int64_t nnz_bou
         return fail(SBC_ERR_INVALID_ARG, "negative or zero size");
     SBC_TRY(check_order(order));
     const bool bf = dtype == SBC_BF16;
-    const Route f = forward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
-    const Route b = backward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
-    plan->forward_order = f == kFwdSpmm ? SBC_ORDER_SPMM_FIRST : SBC_ORDER_GEMM_FIRST;
-    plan->backward_order = b == kBwdD ? SBC_ORDER_SPMM_FIRST : SBC_ORDER_GEMM_FIRST;
-    plan->forward_fused = route_fused(f, M, C_in, C_out, bf) ||
-                                  route_tile(f, M, C_in, C_out, bf, order)
-                              ? 1
-                              : 0;
+    const Route f = forward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf, false);
+    const Route b = backward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf, false);
+    plan->forward_order = f == kFwdGemm ? SBC_ORDER_GEMM_FIRST : SBC_ORDER_SPMM_FIRST;
+    plan->backward_order =
+        b == kBwdD || b == kBwdTileD ? SBC_ORDER_SPMM_FIRST : SBC_ORDER_GEMM_FIRST;
+    plan->forward_fused = f == kFwdTile || route_fused(f, M, C_in, C_out, bf) ? 1 : 0;
     plan->backward_fused = route_fused(b, M, C_in, C_out, bf) ? 1 : 0;
     return SBC_OK;
 }
@@ -314,10 +329,16 @@ extern "C" size_t sbc_conv_workspace_size(int32_t n_out, int32_t n_in, int64_t n
                                           sbc_dtype dtype, sbc_order order) {
     if (n_out < 0 || n_in < 0 || nnz_bound < 0 || M <= 0 || C_in <= 0 || C_out <= 0) return 0;
     const bool bf = dtype == SBC_BF16;
-    const Route f = forward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
-    const Route b = backward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf);
-    const size_t a = route_bytes(f, n_out, n_in, nnz_bound, M, C_in, C_out, bf, order);
-    const size_t c = route_bytes(b, n_out, n_in, nnz_bound, M, C_in, C_out, bf, order);
+    // (with the basis values given, and without)
+    size_t a = 0, c = 0;
+    for (const bool values : {false, true}) {
+        const Route f = forward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf, values);
+        const Route b = backward_route(n_out, n_in, nnz_bound, M, C_in, C_out, order, bf, values);
+        const size_t fb = route_bytes(f, n_out, n_in, nnz_bound, M, C_in, C_out, bf);
+        const size_t bb = route_bytes(b, n_out, n_in, nnz_bound, M, C_in, C_out, bf);
+        a = fb > a ? fb : a;
+        c = bb > c ? bb : c;
+    }
     return a > c ? a : c;
 }
 
@@ -337,22 +358,39 @@ sbc_status tile_geometry(const sbc_csr *csr, const float *v, const sbc_geometry 
     return SBC_OK;
 }
 
-// The forward pass with its temporary space in `workspace` (workspace_bytes of it).
+// The forward's route and the temporary space it needs.  Where the space is
+// fixed (`space` bytes; else SIZE_MAX) a route that does not fit it gives way to
+// the tile pass if that serves the shape.
+Route forward_route_in(const sbc_csr *csr, const float *v, int32_t M, int32_t Ci, int32_t Co,
+                       sbc_order order, bool bf, size_t space, size_t *need) {
+    const int64_t nnz = csr->nnz_bound;
+    Route r = forward_route(csr->n_rows, csr->n_cols, nnz, M, Ci, Co, order, bf, v != nullptr);
+    *need = route_bytes(r, csr->n_rows, csr->n_cols, nnz, M, Ci, Co, bf);
+    if (*need > space && order != SBC_ORDER_GEMM_FIRST && tile_shape(kFwdSpmm, M, Ci, Co, bf)) {
+        r = kFwdTile;
+        *need = route_bytes(r, csr->n_rows, csr->n_cols, nnz, M, Ci, Co, bf);
+    }
+    return r;
+}
+
+// The forward pass with its temporary space in `workspace` (workspace_bytes of
+// it; fixed_space: the caller could not give more).
 sbc_status conv_forward(const sbc_csr *csr, const float *v, const sbc_geometry *geometry,
                         int32_t M, const void *F, const void *W, sbc_dtype dtype, int32_t C_in,
                         int32_t C_out, float *Y, sbc_order order, void *workspace,
-                        size_t workspace_bytes, hipStream_t stream) {
+                        size_t workspace_bytes, bool fixed_space, hipStream_t stream) {
     SBC_TRY(check_conv_args(csr, v, geometry, M, F, W, dtype, C_in, C_out));
     SBC_TRY(check_order(order));
     if (!Y && csr->n_rows > 0) return fail(SBC_ERR_INVALID_ARG, "Y is null");
     if (!aligned16(Y)) return fail(SBC_ERR_INVALID_ARG, "Y must be 16-byte aligned");
     const int32_t n_out = csr->n_rows, n_in = csr->n_cols;
     const bool bf = dtype == SBC_BF16;
-    const Route r = forward_route(n_out, n_in, csr->nnz_bound, M, C_in, C_out, order, bf);
-    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf, order);
+    size_t need;
+    const Route r = forward_route_in(csr, v, M, C_in, C_out, order, bf,
+                                     fixed_space ? workspace_bytes : SIZE_MAX, &need);
     if (!workspace || workspace_bytes < need)
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_conv_workspace_size()");
-    if (route_tile(r, M, C_in, C_out, bf, order)) {
+    if (route_tile(r)) {
         const TileWs ws = carve_tile(workspace, r, n_out, n_in, M, C_in, C_out, bf, nullptr);
         KGeo g;
         int mode;
@@ -427,7 +465,7 @@ extern "C" sbc_status sbc_conv_forward(const sbc_csr *csr, const float *v,
                                        size_t workspace_bytes, hipStream_t stream) {
     clear_error();
     return conv_forward(csr, v, geometry, M, F, W, dtype, C_in, C_out, Y, order, workspace,
-                        workspace_bytes, stream);
+                        workspace_bytes, false, stream);
 }
 
 extern "C" size_t sbc_conv_forward_noalloc_max_bytes(void) { return sbc::kScratchBytes; }
@@ -441,10 +479,8 @@ extern "C" sbc_status sbc_conv_forward_noalloc(const sbc_csr *csr, const float *
     SBC_TRY(check_conv_args(csr, v, geometry, M, F, W, dtype, C_in, C_out));
     SBC_TRY(check_order(order));
     const bool bf = dtype == SBC_BF16;
-    const Route r = forward_route(csr->n_rows, csr->n_cols, csr->nnz_bound, M, C_in, C_out, order,
-                                  bf);
-    const size_t need = route_bytes(r, csr->n_rows, csr->n_cols, csr->nnz_bound, M, C_in, C_out, bf,
-                                    order);
+    size_t need;
+    forward_route_in(csr, v, M, C_in, C_out, order, bf, kScratchBytes, &need);
     if (need > kScratchBytes)
         return fail(SBC_ERR_WORKSPACE, "this forward needs " + std::to_string(need) +
                                            " bytes of temporary space; the library's static "
@@ -453,7 +489,7 @@ extern "C" sbc_status sbc_conv_forward_noalloc(const sbc_csr *csr, const float *
     void *ws = nullptr;
     SBC_TRY(scratch_of_current_device(&ws));
     return conv_forward(csr, v, geometry, M, F, W, dtype, C_in, C_out, Y, order, ws,
-                        kScratchBytes, stream);
+                        kScratchBytes, true, stream);
 }
 
 extern "C" sbc_status sbc_conv_backward(const sbc_csr *csr, const sbc_csc *csc, const float *v,
@@ -481,11 +517,12 @@ extern "C" sbc_status sbc_conv_backward(const sbc_csr *csr, const sbc_csc *csc, 
     if (!dF && !dW) return SBC_OK;
     const int32_t n_out = csr->n_rows, n_in = csr->n_cols;
     const bool bf = dtype == SBC_BF16;
-    const Route r = backward_route(n_out, n_in, csr->nnz_bound, M, C_in, C_out, order, bf);
-    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf, order);
+    const Route r = backward_route(n_out, n_in, csr->nnz_bound, M, C_in, C_out, order, bf,
+                                   v != nullptr);
+    const size_t need = route_bytes(r, n_out, n_in, csr->nnz_bound, M, C_in, C_out, bf);
     if (!workspace || workspace_bytes < need)
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_conv_workspace_size()");
-    if (route_tile(r, M, C_in, C_out, bf, order)) {
+    if (route_tile(r)) {
         const TileWs ws = carve_tile(workspace, r, n_out, n_in, M, C_in, C_out, bf, nullptr);
         KGeo g;
         int mode;
@@ -496,7 +533,7 @@ extern "C" sbc_status sbc_conv_backward(const sbc_csr *csr, const sbc_csc *csc, 
             SBC_TRY(tile_contract(cols, v, g, mode, M, dY, W, true, bf, C_out, C_in, dF, ws.frag,
                                   stream, "bwd_tile_df"));
         if (dW)
-            SBC_TRY(r == kBwdD ? tile_weight_gradient(cols, v, g, mode, M, F, dY, bf, C_in, C_out,
+            SBC_TRY(r == kBwdTileD ? tile_weight_gradient(cols, v, g, mode, M, F, dY, bf, C_in, C_out,
                                                       dW, ws.part, stream, "bwd_tile_dw")
                                : tile_weight_gradient(rows, v, g, mode, M, dY, F, bf, C_in, C_out,
                                                       dW, ws.part, stream, "bwd_tile_dw"));
@@ -608,8 +645,12 @@ DecayTileWs carve_decay_tile(void *base, int32_t n, int32_t M, int32_t Ci, int32
     return w;
 }
 
-bool decay_tile(int32_t M, int32_t Ci, int32_t Co, bool bf) {
-    return tile_available(M, Ci, Co) && !fused_backward_available(M, Ci, Co, bf);
+// Whether it runs as a tile pass (estimated as the one over the transposed
+// pattern; the workspace is sized before that is known to be given).
+bool decay_tile(int32_t n, int64_t nnz, int32_t M, int32_t Ci, int32_t Co, bool bf) {
+    if (!tile_available(M, Ci, Co) || fused_backward_available(M, Ci, Co, bf)) return false;
+    return kTileFavour * tile_dw_us(RouteSize{n, nnz, M, Ci, Co}, bf, false) <=
+           split_dw_us(n, nnz, M, Ci, Co);
 }
 
 DecayWs carve_decay(void *base, int32_t n, int64_t nnz, int32_t M, int32_t Ci, int32_t Co,
@@ -632,7 +673,7 @@ extern "C" size_t sbc_decay_gradient_workspace_size(int32_t n, int64_t nnz_bound
                                                     sbc_dtype dtype) {
     if (n < 0 || nnz_bound < 0 || M <= 0 || C_in <= 0 || C_out <= 0) return 0;
     size_t bytes = 0;
-    if (decay_tile(M, C_in, C_out, dtype == SBC_BF16)) {
+    if (decay_tile(n, nnz_bound, M, C_in, C_out, dtype == SBC_BF16)) {
         carve_decay_tile(nullptr, n, M, C_in, C_out, &bytes);
         return bytes;
     }
@@ -666,7 +707,7 @@ extern "C" sbc_status sbc_conv_decay_gradient(const sbc_csr *csr, const sbc_csc 
         return fail(SBC_ERR_WORKSPACE, "workspace smaller than sbc_decay_gradient_workspace_size()");
     if (n == 0) return fill_i32(reinterpret_cast<int32_t *>(dlambda), 0, M, stream);
     float *dWp;
-    if (decay_tile(M, C_in, C_out, bf)) {
+    if (decay_tile(n, csr->nnz_bound, M, C_in, C_out, bf)) {
         const DecayTileWs ws = carve_decay_tile(workspace, n, M, C_in, C_out, nullptr);
         KGeo g;
         SBC_TRY(make_kgeo(csr, nullptr, geometry, ws.packed, stream, &g));

@@ -109,15 +109,6 @@ bool contract_tall(int32_t M, int32_t n_rows, int32_t N) {
     return ((int64_t)n_rows + 63) / 64 * chunks >= 512;
 }
 
-int32_t dw_splits(int32_t n_rows, int32_t M, int32_t CP, int32_t CQ) {
-    const int32_t pc = 16 * dw_npb(M, CP);
-    const int64_t ny = (int64_t)((CQ + kTileCS - 1) / kTileCS) * ((CP + pc - 1) / pc);
-    const int64_t tiles = ((int64_t)n_rows + 31) / 32;
-    int64_t s = 512 / ny;
-    if (s > tiles) s = tiles;
-    return s < 1 ? 1 : (int32_t)s;
-}
-
 }  // namespace
 
 bool tile_available(int32_t M, int32_t C_in, int32_t C_out) {

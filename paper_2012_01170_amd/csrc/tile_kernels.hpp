@@ -13,8 +13,9 @@
 // Measured against the separate kernels they replace (gather to memory,
 // float32 contraction): 64 ragged clouds of up to 256 points, 16 entries a
 // row, M 8, 128 -> 128 channels, forward 115 -> 57 us, both gradients 186 ->
-// 145 us; 128 clouds of 1024, weighted M 10, 64 -> 64, forward 237 -> 150 us,
-// both gradients 490 -> 350 us.  Errors against float64 fall from 5e-7 to 2e-7
+// 145 us; 128 clouds of 1024, weighted M 10, 64 -> 64, forward 237 -> 134 us,
+// both gradients 490 -> 322 us.  They do not serve all sizes better: which do is
+// estimated (route_cost.hpp).  Errors against float64 fall from 5e-7 to 2e-7
 // (the split products, split.hpp).
 #pragma once
 
@@ -76,8 +77,14 @@ __device__ __forceinline__ void event_entry(int mode, const KGeo &g, int32_t i, 
     }
 }
 
-// u and the weight of an edge of a point basis, float64 rounded once (the
-// monomials are formed where they are used: three float32 roundings at most).
+// u and the weight of an edge of a point basis, each float64 rounded once.  The
+// monomials are formed from them in float32 where they are used (values()), so a
+// value w x y has up to five roundings, of its three factors and two products,
+// where sbc_basis_eval and the separate kernels form it in float64 and round
+// once (basis.hpp): 5 * 2^-24 against 2^-24 of it, and not the same bits.  The
+// differences and 1 - |u|^2, where float32 would cancel, are float64 on both.
+// The results are nearer to float64 than the separate kernels' all the same,
+// whose float32 sums of M C products lose more (5e-7 against 2e-7 in the header).
 // Weight: (1 - |u|^2)^2 (M = 8), (1 - |u|) / W_i (M = 10; 0 where W_i = 0).
 template <int M>
 __device__ __forceinline__ float4 compact_entry(const KGeo &g, int32_t i, int32_t j) {

@@ -6,18 +6,6 @@
 
 namespace sbc {
 
-// Columns a block takes: N rounded up to 32, 64 or 128, halved while twice the
-// blocks still leave a CU to each.  The blocks of a row tile gather for
-// themselves, but on CUs that would idle, and each multiplies fewer columns
-// (256 rows, M 8, 64 -> 128 channels, 5 entries a row: 25.6 -> 18.4 us).  With two
-// blocks a CU the gathers got in each other's way (4096 rows, 45 entries: 59 us
-// in blocks of 128 columns, 57 of 64, 66 of 32).
-inline int32_t contract_columns(int32_t tiles, int32_t N) {
-    int32_t w = N <= 32 ? 32 : N <= 64 ? 64 : 128;
-    while (w > 32 && (int64_t)tiles * ((N + w / 2 - 1) / (w / 2)) <= 256) w /= 2;
-    return w;
-}
-
 template <int M, bool kXbf, StageKind kKind, bool kTall>
 void launch_contract(const TileContractArgs &a, hipStream_t s) {
     const int32_t tiles = grid_for(a.p.n_rows, kTall && kAlwaysTall<kKind> ? 64 : 32);
