@@ -376,7 +376,7 @@ sbc_status sbc_conv_decay_gradient(const sbc_csr *csr, const sbc_csc *csc,
  * Row sums are taken in float64 in a fixed order.  The backward gives
  *   dPhi [M, P] = G~^T dZ   (float32; dZ [n_out, P] float32),
  * with the workspace of sbc_featureless_workspace_size (the blocks' parts of the
- * product).  No pointer needs more than 4-byte alignment.
+ * product, and for more than 128 columns the row sums).  No pointer needs more than 4-byte alignment.
  * ------------------------------------------------------------------------ */
 size_t sbc_featureless_workspace_size(int32_t n_out, int32_t M, int32_t P);
 sbc_status sbc_featureless_forward(const sbc_csr *csr, const float *v,

@@ -155,7 +155,8 @@ __device__ __forceinline__ void cell_sequential(const LifArgs &A, int32_t ox, in
 // for two blocks a CU, one merging while the other's recursions run: 300k
 // events on 128 x 128 pixels, 3 x 3 fields at stride 2 (165 events a cell) take
 // 43 us, against 47 with 16 cells in the whole LDS, and 79 where the 8 cells
-// need two turns (1024 entries).
+// need two turns (1024 entries).  Two blocks a CU leave 128 registers; fields of
+// 4 x 4 and 5 x 5 spill 25 and 58 of theirs.
 template <int K>
 struct LifTile {
     static constexpr int kCells = 8;

@@ -14,6 +14,9 @@ static void launch_one(const TileDwArgs &a, hipStream_t s) {
                        (a.p.n_rows + T::TR - 1) / T::TR, a.part);
 }
 
+// Registers: M = 32 spills 166 to 175 at one wave a SIMD (the weight gradient and
+// the decay gradient of four decays), given values of 16 functions 28 to 36.  Shapes
+// that lose by it go to the separate kernels (route_cost.hpp).
 template <int M, StageKind kKind>
 static void launch_p(bool bf16, const TileDwArgs &a, hipStream_t s) {
     if constexpr (M < 16) {

@@ -6,6 +6,10 @@
 
 namespace sbc {
 
+// Registers: given values of 24 and 32 functions spill (65 to 157, and 320 to 353:
+// the sums of all functions of 16 rows are held at once), bf16 of M = 8 and 10 with
+// tall tiles 8 to 13.  Shapes that lose by it go to the separate kernels
+// (route_cost.hpp).
 template <int M, bool kXbf, StageKind kKind, bool kTall>
 void launch_contract(const TileContractArgs &a, hipStream_t s) {
     const int32_t tiles = grid_for(a.p.n_rows, kTall && kAlwaysTall<kKind> ? 64 : 32);

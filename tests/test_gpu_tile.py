@@ -2,7 +2,10 @@
 contraction in one kernel, any channel counts) under AUTO: against the oracle
 and against the separate-kernel route (order "gemm_first"), at the edges of
 their tiles: rows, slices of 32 channels, column blocks of 16, chunks of 64 and
-128 channels, rows longer than the stage, one row, no edges."""
+128 channels, rows longer than the stage, one row, no edges.  AUTO gives long
+rows, wide chunks and many basis functions at these row counts to the separate
+kernels; test_gpu_routes.py takes those through the tile passes at sizes where
+it does not, and checks by the launches which ran."""
 import numpy as np
 import pytest
 import torch
