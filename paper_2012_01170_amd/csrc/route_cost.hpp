@@ -13,9 +13,9 @@
 // The coefficients are least-squares fits (of the relative error) to 4632
 // measured shapes: 64 to 32768 rows, 4 to 45 entries a row, 8 to 512 channels,
 // every M, bases and values, both types; half of the times are met within 12 %,
-// nine tenths within 30 %.  Over them the choice is 1.8 % from the best of the
+// nine tenths within 30 %.  Over them the choice is 1.9 % from the best of the
 // routes in the mean, and slower by 5 % or more than the better of the separate
-// ones in 6 % of the shapes, where the tile passes alone were in 55 %.
+// ones in 7 % of the shapes, where the tile passes alone were in 55 %.
 #pragma once
 
 #include <cstdint>
@@ -114,7 +114,10 @@ inline double split_dw_us(int32_t n_out, int64_t nnz, int32_t M_, int32_t Ci, in
 
 // The separate kernels are taken where they are estimated this much faster: at
 // equal times the tile pass needs no intermediate in memory and its split
-// products lose less.
-constexpr double kTileFavour = 0.95;
+// products lose less.  Of 593 measured layers of up to 128 channels and 25 entries
+// a row with evaluated bases, forward and gradients together, 0.9 leaves 26 more
+// than 3 % slower than the tile passes and 41 than the separate kernels (0.95: 66
+// and 41, 0.85: 10 and 60).
+constexpr double kTileFavour = 0.9;
 
 }  // namespace sbc

@@ -56,10 +56,12 @@ ROUTES = {
                   False, False),
     "narrowing": (lambda: P(seed=91, c_in=256, c_out=8), False, True),
     "widening": (lambda: P(seed=92, c_in=8, c_out=256), True, False),
-    "square_wide": (lambda: P(seed=93, c_in=128, c_out=128), False, False),
+    "square_wide": (lambda: P(seed=93, c_in=128, c_out=128), True, False),
     "narrowing_bf16": (lambda: P(seed=94, c_in=200, c_out=16, dtype="bf16"), False, True),
     "narrowing_weighted": (lambda: P(seed=95, c_in=300, c_out=9, basis=W10, n_out=40), False, True),
-    "decays4_small": (lambda: E(seed=96, n=1100, c=9, n_decays=4), False, False),
+    "square_wider": (lambda: P(seed=97, c_in=256, c_out=256), False, False),
+    "decays4_small": (lambda: E(seed=96, n=1100, c=9, n_decays=4), True, False),
+    "decays4_long": (lambda: E(seed=98, n=1500, c=12, n_decays=4, window_us=15_000), False, False),
 }
 TILE = ("fwd_fused", "bwd_tile_df", "bwd_tile_dw")
 
