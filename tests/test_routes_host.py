@@ -39,9 +39,9 @@ def test_up_sampling_contracts_first(lib):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_workspace_grows_with_the_entries_bound_only_by_route(lib, dtype):
-    """Sizes at both sides of every change of route are those of a route: never
-    zero, and the tile pass's smaller than the intermediate it avoids."""
+def test_every_shape_has_a_workspace(lib, dtype):
+    """Also at the sizes where nothing is gathered or a tile is all there is; where
+    the forward runs as separate kernels it holds the smaller intermediate."""
     code = L.SBC_BF16 if dtype == torch.bfloat16 else L.SBC_F32
     for M in (4, 8, 10, 16, 24, 32):
         for ci, co in ((8, 8), (33, 40), (128, 128), (512, 8), (8, 512), (512, 512)):
