@@ -45,6 +45,11 @@ CASES = {
 }
 
 
+def _assert_tile_forward(n, nnz, M, ci, co, dtype=torch.float32):
+    """The sizes are ones that the tile pass is chosen for."""
+    assert G.sbc.conv_plan(n, n, nnz, M, ci, co, dtype=dtype)["forward_fused"]
+
+
 def _pattern(w):
     if w["kind"] == "points":
         rp, ci = oracle.points_csr(w["x_in"], w["in_splits"], w["x_out"], w["out_splits"],
@@ -142,6 +147,7 @@ def test_tile_passes_keep_every_nan(bits):
     """A NaN is one by its bits: also one whose payload lies below the upper 16
     bits, as a weight, a feature and an upstream gradient."""
     n, ci, co = 96, 36, 20
+    _assert_tile_forward(n, n, 4, ci, co)
     idx = torch.arange(n + 1, dtype=torch.int32, device=G.DEV)
     csr = G.sbc.CSR(idx, idx[:n].contiguous(), n, n, n)
     csc = G.sbc.csr_transpose(csr)
@@ -175,6 +181,7 @@ def test_tile_passes_on_tiny_operands(k):
     parts' smallest value, beside the float32 sums' 1e-6 (positive terms only,
     so errors do not grow by cancellation)."""
     n, ci, co = 96, 36, 20
+    _assert_tile_forward(n, n, 4, ci, co)
     idx = torch.arange(n + 1, dtype=torch.int32, device=G.DEV)
     csr = G.sbc.CSR(idx, idx[:n].contiguous(), n, n, n)
     csc = G.sbc.csr_transpose(csr)
@@ -231,6 +238,8 @@ def test_tile_height(name):
     rp, ci, v = _pattern(w)
     mean = len(ci) / w["n_out"]
     assert w["n_out"] // 64 >= 512
+    _assert_tile_forward(w["n_out"], len(ci), w["M"], w["C_in"], w["C_out"],
+                         torch.bfloat16 if w["dtype"] == "bf16" else torch.float32)
     wide = w["dtype"] == "f32" and w["C_out"] > 64
     if short is not None:
         assert short == (mean <= (16 if wide else 10))
@@ -257,6 +266,7 @@ def test_tile_columns(n, c_out):
     print(f"[tile columns] {n} {c_out}", flush=True)
     w = P(seed=70, n_clouds=1, n=n, radius=0.3, k_cap=5, c_in=9, c_out=c_out)
     rp, ci, v = _pattern(w)
+    _assert_tile_forward(n, len(ci), w["M"], 9, c_out)
     t = G.to_device(w)
     csr = G.search(w, t)
     csc = G.sbc.csr_transpose(csr)
