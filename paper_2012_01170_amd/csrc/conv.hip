@@ -11,6 +11,7 @@
 // gather-first products as tile passes (tile.hpp); what is left, and the
 // contract-first products, use the generic kernels below, which evaluate the
 // basis into the workspace first when v is NULL.
+#include <cmath>
 #include <mutex>
 #include <string>
 
@@ -213,6 +214,12 @@ double order_macs(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t C
                       : (double)M * Co * (E + (double)n_in * Ci);
 }
 
+// The separate kernels' intermediate of so many rows stays in competition with a
+// tile pass, which has none, below 2^31 elements (8 GiB).
+double if_held(int32_t rows, int32_t M, int32_t C, double us) {
+    return (int64_t)rows * M * C < (int64_t)1 << 31 ? us : HUGE_VAL;
+}
+
 Route forward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t Ci, int32_t Co,
                     sbc_order order, bool bf, bool values) {
     if (order == SBC_ORDER_GEMM_FIRST) return kFwdGemm;
@@ -225,8 +232,10 @@ Route forward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_t
     if (tile_shape(kFwdSpmm, M, Ci, Co, bf) && (n_out <= n_in || by_macs)) {
         const RouteSize s{n_out, nnz, M, Ci, Co};
         const double tile = kTileFavour * tile_contract_us(s, bf, values);
-        const double spmm = split_forward_us(s);
-        const double gemm = order == SBC_ORDER_SPMM_FIRST ? spmm : gemm_first_forward_us(s, n_in);
+        const double spmm = if_held(n_out, M, Ci, split_forward_us(s));
+        const double gemm = order == SBC_ORDER_SPMM_FIRST
+                                ? spmm
+                                : if_held(n_in, M, Co, gemm_first_forward_us(s, n_in));
         if (tile <= spmm && tile <= gemm) return kFwdTile;
         return spmm <= gemm ? kFwdSpmm : kFwdGemm;
     }
@@ -253,8 +262,8 @@ Route backward_route(int32_t n_out, int32_t n_in, int64_t nnz, int32_t M, int32_
             (tile_contract_us(RouteSize{n_in, nnz, M, Co, Ci}, bf, values) +
              tile_dw_us(over_in ? RouteSize{n_in, nnz, M, Ci, Co} : RouteSize{n_out, nnz, M, Co, Ci},
                         bf, values));
-        const double sd = split_d_us(n_in, nnz, M, Ci, Co);
-        const double sg = split_g_us(n_out, nnz, M, Ci, Co);
+        const double sd = if_held(n_in, M, Co, split_d_us(n_in, nnz, M, Ci, Co));
+        const double sg = if_held(n_out, M, Ci, split_g_us(n_out, nnz, M, Ci, Co));
         const bool d_first = order == SBC_ORDER_SPMM_FIRST || sd <= sg;
         if (tile <= (d_first ? sd : sg)) return over_in ? kBwdTileD : kBwdTileG;
         return d_first ? kBwdD : kBwdG;
@@ -650,7 +659,7 @@ DecayTileWs carve_decay_tile(void *base, int32_t n, int32_t M, int32_t Ci, int32
 bool decay_tile(int32_t n, int64_t nnz, int32_t M, int32_t Ci, int32_t Co, bool bf) {
     if (!tile_available(M, Ci, Co) || fused_backward_available(M, Ci, Co, bf)) return false;
     return kTileFavour * tile_dw_us(RouteSize{n, nnz, M, Ci, Co}, bf, false) <=
-           split_dw_us(n, nnz, M, Ci, Co);
+           if_held(n, M, Ci, split_dw_us(n, nnz, M, Ci, Co));
 }
 
 DecayWs carve_decay(void *base, int32_t n, int64_t nnz, int32_t M, int32_t Ci, int32_t Co,

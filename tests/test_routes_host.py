@@ -53,3 +53,14 @@ def test_every_shape_has_a_workspace(lib, dtype):
                     if ops.conv_plan(n, n, n * deg, M, ci, co, dtype=dtype)["forward_fused"]:
                         continue
                     assert size >= n * M * min(ci, co) * 4
+
+
+def test_intermediates_past_2_to_the_31_stay_on_the_tile_pass(lib):
+    """Rows times M times channels: the separate kernels compete below 2^31."""
+    n = (1 << 31) // (4 * 512)
+    for rows, fused in ((n - 1, False), (n, True)):
+        p = ops.conv_plan(rows, rows, rows * 40, 4, 512, 512)
+        assert p["forward_fused"] == fused
+        size = lib.sbc_conv_workspace_size(rows, rows, rows * 40, 4, 512, 512, L.SBC_F32,
+                                           L.SBC_ORDER_AUTO)
+        assert (size < 4 * rows * 4 * 512) == fused
